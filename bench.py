@@ -288,8 +288,13 @@ def bench_split(torch, mms, grid, x, c_box4, c_box3, dev):
             else:
                 # the method's 2 (2r+1)^3 flop per point against the MFMA peak, and the
                 # issued 16x16x32 MFMA work (Toeplitz band, split products) beside it
-                nch = -(-((2 * r + 1) * 24) // 32)
-                mfma_per_tile = (3 if prec != "bf16x1" else 1) * (2 * r + 1) * nch
+                # a 4 x 4 tile's window of one dz is 3 (r + 2) 8-cell words, four per MFMA: whole
+                # steps once per product, left-over words of the three products packed together
+                full, rem = divmod(3 * (r + 2), 4)
+                terms = 3 if prec != "bf16x1" else 1
+                per_dz = terms * (full + 1) if rem == 3 else terms * full + (
+                    min(rem, terms) if rem else 0)
+                mfma_per_tile = (2 * r + 1) * per_dz
                 issued = gpts * 1e9 / 256 * mfma_per_tile * 16 * 16 * 32 * 2 / 1e12
                 e["mfma_algorithmic_frac"] = e["algorithmic_tflops"] / MFMA_BF16_PEAK_TF
                 e["mfma_issued_tflops"] = issued

@@ -65,7 +65,8 @@ extern "C" {
 #define MMS_BF16X3 1   /* MFMA, BF16 hi+lo split of data and weights, 3 products,   */
                        /* FP32 accumulation                                          */
 #define MMS_FP16X3S 2  /* MFMA, FP16 hi+lo split with a power-of-two scale per      */
-                       /* thread block (data) and per call (weights), 3 products    */
+                       /* thread block and step of planes (data) and per call       */
+                       /* (weights), 3 products                                      */
 #define MMS_BF16X1 3   /* MFMA, BF16 hi*hi only: reduced-accuracy reference variant  */
 
 typedef struct mms_grid {
@@ -88,9 +89,10 @@ typedef struct mms_grid {
  * in, out: device grids with the same layout g; out's halo is not written; in
  * and out must not overlap (MMS_EINVAL).  coeffs: HOST pointer, read during the
  * call only.  radius: 1..4.  precision: MMS_FP32 for the star and the 2-D
- * shapes; any of the four for the box.  The box MFMA variants recast each (dz, dy) pair of the sweep as
- * a banded Toeplitz product along x, the matrix-unit mapping of Sec. IV-A, with
- * the (2r+1)^2 one-dimensional stencils of the box decomposition of Sec. IV-C.
+ * shapes; any of the four for the box.  The box MFMA variants recast each dz of the sweep as a
+ * banded Toeplitz product over (y, x), the matrix-unit mapping of Sec. IV-A with the
+ * one-dimensional stencils of the box decomposition of Sec. IV-C taken 4 x 4 outputs at a time.
+ * There a NaN or Inf input cell makes NaN of outputs up to r + 3 cells away in y and 7 in x.
  * An FP32 box of radius 2-4 addresses a tile of (32 + 2r + 1) rows with 32-bit
  * offsets: a pitch sy with (33 + 2r) * sy >= 2^32 gives MMS_EUNSUPPORTED.
  */

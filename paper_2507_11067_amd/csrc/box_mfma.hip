@@ -2,33 +2,39 @@
 //
 // The paper maps a one-dimensional stencil onto an outer-product matrix unit by
 // multiplying the input rows with a zero-padded coefficient column (Sec. IV-A);
-// written as a matrix product this is  out_row = T * in_window  with T a banded
-// Toeplitz matrix.  The box is (2r+1)^2 such one-dimensional stencils, one per
-// (dz, dy) pair (Sec. IV-C).  Here every (dz, dy) pair becomes a 16 x 24 Toeplitz
-// block along x,
-//     T_{dz,dy}[m][x'] = c[dz][dy][x' - 4 - m]   (zero outside |x' - 4 - m| <= r),
-// and the 2r+1 dy blocks of one dz are laid side by side along K:
-//     D(16 x, 16 y) += [T_{dz,-r} .. T_{dz,r}] * [In_{z+dz}(rows y-r..) ; ... ; In(rows y+r..)]
-// K per dz is (2r+1)*24, cut into 32-wide steps ("chunks") of
-// v_mfma_f32_16x16x32_{bf16,f16}; A = Toeplitz fragment, B = input fragment.
+// written as a matrix product this is  out = T * in_window  with T a banded
+// Toeplitz matrix.  Here the Toeplitz block of one dz is two-dimensional: its 16
+// rows are the outputs of a 4 x 4 tile of (y, x), its columns the tile's window of
+// (4 + 2r) x 12 input cells,
+//     T_dz[(my, mx)][(y', x')] = c[dz][y' - r - my][x' - 4 - mx]   (zero outside the box),
+// and the 16 columns of the other operand are 16 such tiles side by side along x:
+//     D(4 x 4 cells, 16 x-blocks) += T_dz * In_{z+dz}(window of each block).
+// A fraction (2r+1)^2 / (12 (4 + 2r)) of the products is useful (56 % at radius 4), where
+// a one-dimensional block of 16 x-outputs per dy leaves (2r+1) / 24 (37 %): 126 against
+// 189 MFMAs of 16 x 16 x 32 per 256 outputs at radius 4, 84 against 126 at radius 3, which
+// took the 512^3 sweep from 1090 to 742 us and from 711 to 524.
 //
 // FP32 accuracy from 16-bit multipliers: every operand x is split as x = hi + lo
 // (BF16: hi = RN(x), lo = RN(x - hi); FP16: the same after scaling by a power of
 // two that keeps the block's largest |x| below 2^14), and each product is
-// formed as hi*hi + hi*lo + lo*hi with FP32 accumulation (lo*lo is dropped).
-// The BF16X1 variant keeps hi*hi only.
+// formed as hi*hi + hi*lo + lo*hi with FP32 accumulation (lo*lo is dropped, except
+// where a step has slots to spare).  The BF16X1 variant keeps hi*hi only.
 //
-// Work split.  A block of NW waves owns a (16*NT) x (16*NW) output tile of the (x, y)
-// plane and streams a chunk of z.  All Toeplitz fragments (hi and lo, every dz
-// and chunk) are built once per block into LDS.  One input plane at a time sits
-// in LDS as hi/lo 16-bit arrays.  Each wave owns NT 16x16 tiles (16 rows) and
-// walks the full K: per chunk it loads the NT input fragments once and reuses
-// them for every dz and product (input plane z' feeds output z' - dz), and each
-// Toeplitz fragment pair it loads feeds NT tiles.  A wave therefore keeps 2r+1
-// output planes of accumulators in flight; after each input plane the oldest is
-// complete, is written, and the window shifts by one.  The next input plane is
-// requested from memory one plane ahead, so its latency hides behind a whole
-// plane of MFMA work.
+// Work split.  A block of 8 waves owns a 64 x (32 NT) output tile of the (x, y) plane and
+// streams a chunk of z, PZ input planes per step.  All Toeplitz fragments (hi and lo, every
+// dz) are built once per block into LDS.  The planes of a step sit in LDS as 16-bit hi and
+// lo parts, the 4-cell words of two neighbouring rows side by side ("pair words"), so that
+// a lane's eight K values are one 16-byte read and the 16 lanes of a group read 256
+// consecutive bytes.  Each wave owns NT tiles of 64 x 4 outputs; per K step it loads the
+// input fragments once and reuses them for every dz and product (input plane z' feeds
+// output z' - dz), and each Toeplitz fragment it loads feeds NT * PZ tiles.  A wave keeps
+// 2r + PZ output planes of accumulators in flight; after each step the PZ oldest are
+// complete, are written, and the window shifts.  The next step's planes are requested a
+// whole step ahead and split halfway through it.  (step, dz) units that feed no output of
+// the chunk are skipped, which matters where chunks are short.
+//
+// The kernel is bound by the matrix cores: at 512^3, radius 4, it issues 1.46 PFLOP/s of
+// MFMA work (a large BF16 matrix product reaches 1.2 PFLOP/s on the same card).
 #include <hip/hip_runtime.h>
 
 #include "mms_internal.h"
@@ -40,15 +46,21 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// Launch shape per radius: NW waves per block (one 16-row band each), NT 16x16
-// tiles per wave along x.  The block's Toeplitz fragments take 2 KB per (dz,
-// chunk) unit of LDS, so radius 4 (63 units) leaves room for 4 waves only
-// (4 tiles each); up to radius 3, 8 waves of 2 tiles fit and two waves share
-// each SIMD (measured at 512^3: +9 % at radius 3, +19 % at radius 2).
+// Launch shape per radius: 8 waves per block (two per SIMD, so that one wave's loads,
+// splits and stores run beside the other's MFMAs), NT tiles of 64 x 4 outputs per wave
+// along y, PZ input planes per step.  Every Toeplitz fragment read from LDS feeds
+// NT * PZ tiles, and these reads are what LDS has to carry: at NT * PZ = 2 they take 84 %
+// of its cycles at radius 4, at 4 less than half.  The product 4 as one row of tiles and
+// four planes keeps the block's tile at 64 x 32 (more blocks for small grids, longer z
+// chunks for large ones).  Measured, BF16X3, 512^3 / 300 x 301 x 290, us (NT, PZ): radius 4
+// 742 / 158 (1, 4), 791 / 176 (2, 2), 768 / 172 (2, 1); radius 3 524 (1, 4), 529 (2, 2),
+// 561 (2, 1).  Up to radius 2 the fragments are few enough that the compiler keeps them in
+// registers and spills at (1, 4) (1188 at radius 2); (2, 2) runs at 343.
 template <int R>
 struct MCfg {
-    static constexpr int NW = R == 4 ? 4 : 8;
-    static constexpr int NT = R == 4 ? 4 : 2;
+    static constexpr int NW = 8;
+    static constexpr int NT = R >= 3 ? 1 : 2;
+    static constexpr int PZ = R >= 3 ? 4 : 2;
 };
 
 struct MfmaArgs {
@@ -88,40 +100,46 @@ __device__ __forceinline__ floatx4 mfma(const uint4 &a, const uint4 &b, floatx4 
     }
 }
 
-template <int R, int NW, int NT>
+// K layout of one dz: 16-byte words of LDS, each holding 4 x-cells of two neighbouring
+// rows ("pair words").  The window of a 4 x 4 output tile is 4 + 2r rows by 12 cells, so
+// NP = 3 (2 + r) pair words; one MFMA step takes four of them (one per lane group).
+template <int R>
 struct Shape {
-    static constexpr int BXT = 16 * NT;
-    static constexpr int BYT = 16 * NW;
+    static constexpr int NW = MCfg<R>::NW, NT = MCfg<R>::NT, PZ = MCfg<R>::PZ;
+    static constexpr int BXT = 64;                  // 16 x-blocks of 4 cells (N)
+    static constexpr int BYT = 4 * NT * NW;         // 4 rows per tile (M = 4 x 4 cells)
     static constexpr int Q = 2 * R + 1;             // output planes in flight, dz values
-    static constexpr int WX = 24;                   // x window per dy (16 + 2r <= 24)
-    static constexpr int NCH = (Q * WX + 31) / 32;  // 32-wide K steps per dz
-    static constexpr int NU = Q * NCH;              // Toeplitz fragment pairs
-    static constexpr int LR = BYT + 2 * R;          // LDS rows of a plane
-    // LDS row pitch in 16-bit cells, >= BXT + 8 with 2*LP bytes = 16 mod 128, so the 16-byte B-fragment
-    // reads of 8 consecutive rows land on 8 distinct groups of 4 banks
-    static constexpr int LP = (BXT + 63) / 64 * 64 + 8;
-    static constexpr int C4 = BXT / 4 + 2;          // float4 per staged row
-    static constexpr int NS = LR * C4;              // float4 per staged plane
-    static constexpr int NSK = (NS + 64 * NW - 1) / (64 * NW);
+    static constexpr int NP = 3 * (2 + R);          // pair words of a tile's window
+    // whole steps of four words; three left-over words take a whole step too
+    static constexpr int NCH = NP % 4 == 3 ? NP / 4 + 1 : NP / 4;
+    static constexpr int REM = NP % 4 == 3 ? 0 : NP % 4;   // 0, 1 or 2 words left over
+    // A fragments per dz: hi and lo of each step, and those of the left-over words
+    // (one word: its three products share one step; two words: two steps)
+    static constexpr int NA = 2 * NCH + REM;
+    static constexpr int NPR = (BYT + 2 * R) / 2;   // LDS row pairs of a plane
+    static constexpr int C4 = BXT / 4 + 2;          // words per row pair
+    static constexpr int NS = NPR * C4;             // pair words per plane
+    static constexpr int NSK = (PZ * NS + 64 * NW - 1) / (64 * NW);
 };
 
-template <int R, int NW, int NT>
+template <int R>
 struct Smem {
-    using S = Shape<R, NW, NT>;
-    uint4 afrag[S::NU][2][64];   // [unit][hi, lo][lane]
-    uint16_t dhi[S::LR][S::LP];
-    uint16_t dlo[S::LR][S::LP];
-    float smax[NW];
+    using S = Shape<R>;
+    static constexpr int PZ = S::PZ;
+    uint4 afrag[S::Q][S::NA][64];   // [dz][fragment][lane]
+    uint4 d[2][PZ][S::NPR][S::C4];  // hi and lo parts of the planes
+    float smax[S::NW];
 };
 
-template <int R, int PREC, int NW, int NT>
-__global__ void __launch_bounds__(64 * NW) box_mfma_kernel(MfmaArgs a) {
-    using S = Shape<R, NW, NT>;
+template <int R, int PREC>
+__global__ void __launch_bounds__(64 * MCfg<R>::NW) box_mfma_kernel(MfmaArgs a) {
+    using S = Shape<R>;
     constexpr int BXT = S::BXT, BYT = S::BYT;
-    constexpr int Q = S::Q, NCH = S::NCH, C4 = S::C4, NS = S::NS, NSK = S::NSK, WX = S::WX;
+    constexpr int Q = S::Q, NCH = S::NCH, C4 = S::C4, NS = S::NS, NSK = S::NSK;
+    constexpr int REM = S::REM, NP = S::NP, NW = S::NW, NT = S::NT, PZ = S::PZ;
     constexpr int NTH = 64 * NW;
     constexpr bool SPLIT3 = PREC != MMS_BF16X1;
-    __shared__ Smem<R, NW, NT> sm;
+    __shared__ Smem<R> sm;
 
     const Geom &g = a.g;
     int b = mms_xcd_remap(blockIdx.x, gridDim.x);
@@ -136,34 +154,101 @@ __global__ void __launch_bounds__(64 * NW) box_mfma_kernel(MfmaArgs a) {
     const int zb = zci * g.zchunk;
     const int ze = min(zb + g.zchunk, g.nz);
     const int nx4 = (g.nx + 3) & ~3;
-    const int ylim = g.ny + g.H;
+    const int ylim = g.ny + R;   // rows beyond the stencil's reach stay out of the products
     const int64_t sy = g.sy, sz = g.sz;
 
-    // staging items: float4 (row, col4) of the plane window
+    // staging items: the two float4 of a pair word
+    int s_z[NSK];
     int64_t s_off[NSK];
-    bool s_ok[NSK];
+    bool s_ok[NSK][2];
 #pragma unroll
     for (int k = 0; k < NSK; ++k) {
         const int i = tid + k * NTH;
-        const int row = i / C4, col = i % C4;
-        const int yy = yt - R + row, xx = xt - 4 + 4 * col;
-        s_ok[k] = (i < NS) && (yy < ylim) && (xx <= nx4);
+        const int rp = i % NS / C4, col = i % NS % C4;
+        const int yy = yt - R + 2 * rp, xx = xt - 4 + 4 * col;
+        s_z[k] = i / NS;
+        s_ok[k][0] = (i < PZ * NS) && (yy < ylim) && (xx <= nx4);
+        s_ok[k][1] = (i < PZ * NS) && (yy + 1 < ylim) && (xx <= nx4);
         s_off[k] = (int64_t)yy * sy + xx;
     }
     const int z_first = zb - R, z_last = ze + R;
 
-    // FP16 path: one power-of-two scale per block from the largest |x| it reads
-    float dscale = 1.0f;
-    if constexpr (PREC == MMS_FP16X3S) {
-        float m = 0.f;
-        for (int zi = z_first; zi < z_last; ++zi) {
-            const float *p = g.in0 + (int64_t)zi * sz;
-#pragma unroll
-            for (int k = 0; k < NSK; ++k) {
-                const float4 v = guarded_load(p + s_off[k], s_ok[k], g.in0);
-                m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
-            }
+    const float cscale = (PREC == MMS_FP16X3S) ? a.cscale : 1.0f;
+
+    // Toeplitz fragments of every dz into LDS (A operand), from a copy of the weights that
+    // borrows the plane buffer
+    float *cl = reinterpret_cast<float *>(&sm.d[0][0][0][0]);
+    static_assert(sizeof(sm.d) >= Q * Q * Q * sizeof(float));
+    for (int i = tid; i < Q * Q * Q; i += NTH) cl[i] = a.c[i];
+    __syncthreads();
+    for (int item = tid; item < Q * S::NA * 64; item += NTH) {
+        const int l = item & 63, f = (item >> 6) % S::NA, dz = (item >> 6) / S::NA;
+        const int m = l & 15, grp = l >> 4;
+        const int my = m >> 2, mx = m & 3;
+        // the word and part (hi or lo) of this lane group's slot
+        int w, part;
+        bool on = true;
+        if (f < 2 * NCH) {
+            w = 4 * (f >> 1) + grp;
+            part = f & 1;
+        } else if (REM == 1) {          // slots hi*hi, hi*lo, lo*hi
+            w = 4 * NCH;
+            part = grp == 2;
+            on = SPLIT3 ? grp < 3 : grp == 0;
+        } else {                        // slots hi, hi of the data, lo, lo of the data
+            w = 4 * NCH + (grp & 1);
+            part = f - 2 * NCH;
+            on = SPLIT3 || grp < 2;
         }
+        uint32_t o[4];
+#pragma unroll
+        for (int j2 = 0; j2 < 4; ++j2) {
+            uint16_t p[2];
+#pragma unroll
+            for (int j1 = 0; j1 < 2; ++j1) {
+                const int j = 2 * j2 + j1;
+                const int dy = 2 * (w / 3) + (j >> 2) - R - my;
+                const int dx = 4 * (w % 3) + (j & 3) - 4 - mx;
+                float v = 0.f;
+                if (on && w < NP && dy >= -R && dy <= R && dx >= -R && dx <= R)
+                    v = cl[(dz * Q + dy + R) * Q + dx + R];
+                uint16_t h, lo;
+                split<PREC>(v, cscale, h, lo);
+                p[j1] = part ? lo : h;
+            }
+            o[j2] = p[0] | (uint32_t)p[1] << 16;
+        }
+        sm.afrag[dz][f][l] = make_uint4(o[0], o[1], o[2], o[3]);
+    }
+
+    float4 stage[NSK][2];
+    uint4 shi[NSK], slo[NSK];   // the staged plane split into packed 16-bit hi and lo parts
+    auto load_plane = [&](int z) {
+#pragma unroll
+        for (int k = 0; k < NSK; ++k) {
+            const float *p = g.in0 + (int64_t)min(z + s_z[k], z_last - 1) * sz + s_off[k];
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                stage[k][j] = guarded_load(p + j * sy, s_ok[k][j], g.in0);
+        }
+    };
+    // FP16 path: one power-of-two scale per block and step, from the largest finite |x| that
+    // the block has staged so far.  It only changes when a step brings a larger value: the
+    // accumulators, which hold sums in units of dscale * cscale, are then rescaled (exactly).
+    // A scan of the block's whole window before the first product would cost a second read
+    // of the grid (0.15 of 0.9 ms at 512^3, radius 4).
+    float dscale = 1.0f, dnext = 1.0f, dmax = 0.f;
+    auto scale_step = [&]() {
+        float m = 0.f;
+#pragma unroll
+        for (int k = 0; k < NSK; ++k)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float4 v = stage[k][j];
+                const float e[4] = {fabsf(v.x), fabsf(v.y), fabsf(v.z), fabsf(v.w)};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) m = e[i] <= 3.402823466e38f ? fmaxf(m, e[i]) : m;
+            }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
         if (lane == 0) sm.smax[wave] = m;
@@ -171,154 +256,165 @@ __global__ void __launch_bounds__(64 * NW) box_mfma_kernel(MfmaArgs a) {
         m = sm.smax[0];
 #pragma unroll
         for (int w = 1; w < NW; ++w) m = fmaxf(m, sm.smax[w]);
-        if (m > 0.f && m < 3.0e38f) {
+        if (m > dmax) {
+            dmax = m;
             int e;
             frexpf(m, &e);  // m = f 2^e, 0.5 <= f < 1
-            dscale = ldexpf(1.0f, 14 - e);
+            dnext = ldexpf(1.0f, min(14 - e, 100));
         }
-    }
-    const float cscale = (PREC == MMS_FP16X3S) ? a.cscale : 1.0f;
-
-    // Toeplitz fragments of every (dz, chunk) into LDS (A operand)
-    for (int item = tid; item < S::NU * 64; item += NTH) {
-        const int u = item >> 6, l = item & 63;
-        const int dz = u / NCH, ch = u % NCH;
-        const int m = l & 15, grp = l >> 4;
-        uint16_t h[8], lo[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int k = 32 * ch + 8 * grp + j;
-            const int dyi = k / WX, xp = k % WX;
-            const int dx = xp - 4 - m;
-            float v = 0.f;
-            if (dyi < Q && dx >= -R && dx <= R) v = a.c[(dz * Q + dyi) * Q + dx + R];
-            split<PREC>(v, cscale, h[j], lo[j]);
-        }
-        sm.afrag[u][0][l] = make_uint4(h[0] | (uint32_t)h[1] << 16, h[2] | (uint32_t)h[3] << 16,
-                                       h[4] | (uint32_t)h[5] << 16, h[6] | (uint32_t)h[7] << 16);
-        sm.afrag[u][1][l] = make_uint4(lo[0] | (uint32_t)lo[1] << 16, lo[2] | (uint32_t)lo[3] << 16,
-                                       lo[4] | (uint32_t)lo[5] << 16, lo[6] | (uint32_t)lo[7] << 16);
-    }
-
-    float4 stage[NSK];
-    uint2 shi[NSK], slo[NSK];   // the staged plane split into packed 16-bit hi and lo parts
-    auto load_plane = [&](int z) {
-        const float *p = g.in0 + (int64_t)z * sz;
-#pragma unroll
-        for (int k = 0; k < NSK; ++k) stage[k] = guarded_load(p + s_off[k], s_ok[k], g.in0);
     };
-    // the split runs while the previous plane's MFMAs execute; only the LDS writes wait
+    // the split runs while the previous step's MFMAs execute; only the LDS writes wait
     // for the barrier that frees the plane buffer
     auto split_plane = [&]() {
 #pragma unroll
         for (int k = 0; k < NSK; ++k) {
-            uint16_t h0, l0, h1, l1, h2, l2, h3, l3;
-            split<PREC>(stage[k].x, dscale, h0, l0);
-            split<PREC>(stage[k].y, dscale, h1, l1);
-            split<PREC>(stage[k].z, dscale, h2, l2);
-            split<PREC>(stage[k].w, dscale, h3, l3);
-            shi[k] = make_uint2(h0 | (uint32_t)h1 << 16, h2 | (uint32_t)h3 << 16);
-            slo[k] = make_uint2(l0 | (uint32_t)l1 << 16, l2 | (uint32_t)l3 << 16);
+            uint32_t h[4], l[4];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                uint16_t h0, l0, h1, l1, h2, l2, h3, l3;
+                split<PREC>(stage[k][j].x, dnext, h0, l0);
+                split<PREC>(stage[k][j].y, dnext, h1, l1);
+                split<PREC>(stage[k][j].z, dnext, h2, l2);
+                split<PREC>(stage[k][j].w, dnext, h3, l3);
+                h[2 * j] = h0 | (uint32_t)h1 << 16;
+                h[2 * j + 1] = h2 | (uint32_t)h3 << 16;
+                l[2 * j] = l0 | (uint32_t)l1 << 16;
+                l[2 * j + 1] = l2 | (uint32_t)l3 << 16;
+            }
+            shi[k] = make_uint4(h[0], h[1], h[2], h[3]);
+            slo[k] = make_uint4(l[0], l[1], l[2], l[3]);
         }
     };
     auto write_plane = [&]() {
 #pragma unroll
         for (int k = 0; k < NSK; ++k) {
             const int i = tid + k * NTH;
-            if (i < NS) {
-                const int row = i / C4, col = i % C4;
-                *reinterpret_cast<uint2 *>(&sm.dhi[row][4 * col]) = shi[k];
-                *reinterpret_cast<uint2 *>(&sm.dlo[row][4 * col]) = slo[k];
+            if (i < PZ * NS) {
+                (&sm.d[0][0][0][0])[i] = shi[k];
+                if (SPLIT3) (&sm.d[1][0][0][0])[i] = slo[k];
             }
         }
     };
 
     // acc[k][t] holds the partial sum of output plane zi - R + k
-    floatx4 acc[Q][NT];
+    constexpr int NQ = Q + PZ - 1;
+    floatx4 acc[NQ][NT];
 #pragma unroll
-    for (int s = 0; s < Q; ++s)
+    for (int s = 0; s < NQ; ++s)
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[s][t] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    const int n = lane & 15, grp = lane >> 4;   // B fragment: output row n, K group grp
-    const int wrow = 16 * wave;
-    const float outscale = 1.0f / (dscale * cscale);
+    const int n = lane & 15, grp = lane >> 4;   // B fragment: x-block n, word slot grp
+    const int wrow = 4 * NT * wave;             // the wave's first row in the tile
+
+    // word offsets of the lane's B fragments: step ch, and the left-over words
+    const uint4 *bbase = &sm.d[0][0][wrow / 2][n];
+    int boff[NCH], brem = 0;
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+        const int w = 4 * ch + grp < NP ? 4 * ch + grp : 0;   // a zero-weight slot reads word 0
+        boff[ch] = (w / 3) * C4 + w % 3;
+    }
+    if constexpr (REM > 0) {
+        const int w = 4 * NCH + (REM == 2 ? grp & 1 : 0);
+        const bool lo = SPLIT3 && (REM == 2 ? grp >= 2 : grp == 1);
+        brem = (w / 3) * C4 + w % 3 + (lo ? PZ * S::NS : 0);
+    }
 
     load_plane(z_first);
+    if constexpr (PREC == MMS_FP16X3S) scale_step();
     split_plane();
+    dscale = dnext;
+    __syncthreads();   // the weights' copy is read
     write_plane();
-    if (z_first + 1 < z_last) load_plane(z_first + 1);
+    if (z_first + PZ < z_last) load_plane(z_first + PZ);
     __syncthreads();
-    // B fragments of chunk ch (hi and lo) into buffer set `buf`
-    uint4 bh[2][NT], bl[2][NT];
-    auto load_b = [&](int ch, int buf) {
-        const int k0 = 32 * ch + 8 * grp;
-        const int dyi = k0 / WX, xg = (k0 % WX) / 8;
-        const bool kval = dyi < Q;
-        // the padded tail of K reads a valid row and is masked to zero
-        const uint32_t km = kval ? 0xffffffffu : 0u;
-        const int row = wrow + n + (kval ? dyi : 0);
+
+    uint4 bh[PZ][NT], bl[PZ][NT];
+    auto load_b = [&](int ch) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const uint4 h = *reinterpret_cast<const uint4 *>(&sm.dhi[row][16 * t + 8 * xg]);
-            bh[buf][t] = make_uint4(h.x & km, h.y & km, h.z & km, h.w & km);
-            if constexpr (SPLIT3) {
-                const uint4 l = *reinterpret_cast<const uint4 *>(&sm.dlo[row][16 * t + 8 * xg]);
-                bl[buf][t] = make_uint4(l.x & km, l.y & km, l.z & km, l.w & km);
+        for (int j = 0; j < PZ; ++j)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const uint4 *p = bbase + (ch < NCH ? boff[ch] : brem) + 2 * t * C4 + j * NS;
+                bh[j][t] = *p;
+                if (SPLIT3 && ch < NCH) bl[j][t] = p[PZ * NS];
             }
-        }
     };
-    // A fragments of unit u = ch * Q + (dz + R) into ring slot `slot`
-    constexpr int PF = 3;   // A-fragment ring: unit u+2 is requested while unit u computes
+    // units: (step, dz) pairs, then the left-over words of every dz
+    constexpr int NU = Q * (NCH + (REM > 0));
+    constexpr int PF = 2;   // A fragments one unit ahead
     uint4 ah[PF], al[PF];
     auto load_a = [&](int u, int slot) {
         const int ch = u / Q, dzi = u % Q;
-        ah[slot] = sm.afrag[dzi * NCH + ch][0][lane];
-        if constexpr (SPLIT3) al[slot] = sm.afrag[dzi * NCH + ch][1][lane];
+        ah[slot] = sm.afrag[dzi][2 * ch][lane];
+        if (ch < NCH ? SPLIT3 : REM == 2 && SPLIT3) al[slot] = sm.afrag[dzi][2 * ch + 1][lane];
     };
 
-    for (int zi = z_first; zi < z_last; ++zi) {
-        // software pipeline over the (chunk, dz) units of this plane: the next chunk's B
-        // fragments and the A fragments two units ahead are in flight while a unit's
-        // 3 x NT MFMAs issue
-        load_b(0, 0);
-        load_a(0, 0);
-        if (S::NU > 1) load_a(1, 1);
+    for (int zi = z_first; zi < z_last; zi += PZ) {
+        // keeps the fragment reads in the loop (hoisted out of it they spill)
+        asm volatile("" ::: "memory");
+        load_b(0);
 #pragma unroll
-        for (int u = 0; u < S::NU; ++u) {
+        for (int u = 0; u < PF - 1; ++u) load_a(u, u);
+        const int dlo = __builtin_amdgcn_readfirstlane(zi - ze + R + 1);
+        const int dhi = __builtin_amdgcn_readfirstlane(zi - zb + R + PZ - 1);
+        auto unit = [&](int u) {
             const int ch = u / Q, dzi = u % Q;
-            if (dzi == 0 && ch + 1 < NCH) load_b(ch + 1, (ch + 1) & 1);
-            if (u + 2 < S::NU) load_a(u + 2, (u + 2) % PF);
-            if (u == S::NU / 2 && zi + 1 < z_last) split_plane();   // plane zi + 1
+            if (dzi == 0 && u > 0) load_b(ch);
+            if (u + PF - 1 < NU) load_a(u + PF - 1, (u + PF - 1) % PF);
             // keep the requests above this unit's MFMAs (the scheduler would sink them)
             __builtin_amdgcn_sched_barrier(0);
             const uint4 &ahi = ah[u % PF];
-            // input plane zi feeds output zi - dz (dz = dzi - R), held in acc[Q - 1 - dzi]
-            floatx4 *ac = acc[Q - 1 - dzi];
-            const uint4 *bhi = bh[ch & 1];
+            const uint4 &alo = al[u % PF];
+            // input plane zi + j feeds output zi + j - dz (dz = dzi - R), held in
+            // acc[Q - 1 - dzi + j]; units that feed no output of the chunk are skipped
+            if (dzi >= dlo && dzi <= dhi) {
 #pragma unroll
-            for (int t = 0; t < NT; ++t) ac[t] = mfma<PREC>(ahi, bhi[t], ac[t]);
-            if constexpr (SPLIT3) {
-                const uint4 &alo = al[u % PF];
-                const uint4 *blo = bl[ch & 1];
+                for (int j = 0; j < PZ; ++j)
 #pragma unroll
-                for (int t = 0; t < NT; ++t) ac[t] = mfma<PREC>(ahi, blo[t], ac[t]);
+                    for (int t = 0; t < NT; ++t)
+                        acc[Q - 1 - dzi + j][t] = mfma<PREC>(ahi, bh[j][t], acc[Q - 1 - dzi + j][t]);
+                if (SPLIT3 && ch < NCH) {
 #pragma unroll
-                for (int t = 0; t < NT; ++t) ac[t] = mfma<PREC>(alo, bhi[t], ac[t]);
+                    for (int j = 0; j < PZ; ++j)
+#pragma unroll
+                        for (int t = 0; t < NT; ++t)
+                            acc[Q - 1 - dzi + j][t] = mfma<PREC>(ahi, bl[j][t], acc[Q - 1 - dzi + j][t]);
+                }
+                if (SPLIT3 && (ch < NCH || REM == 2)) {
+#pragma unroll
+                    for (int j = 0; j < PZ; ++j)
+#pragma unroll
+                        for (int t = 0; t < NT; ++t)
+                            acc[Q - 1 - dzi + j][t] = mfma<PREC>(alo, bh[j][t], acc[Q - 1 - dzi + j][t]);
+                }
             }
+        };
+#pragma unroll
+        for (int u = 0; u < NU / 2; ++u) unit(u);
+        if (zi + PZ < z_last) {   // the next step's planes
+            if constexpr (PREC == MMS_FP16X3S) scale_step();
+            split_plane();
         }
-        // output plane zi - R is complete (outputs outside [zb, ze) are dropped)
-        const int zo = zi - R;
-        if (zo >= zb && zo < ze) {
-            const int y = yt + wrow + n;
+#pragma unroll
+        for (int u = NU / 2; u < NU; ++u) unit(u);
+        // output planes zi - R .. zi - R + PZ - 1 are complete (those outside [zb, ze) are dropped)
+        const float od = 1.0f / dscale, oc = 1.0f / cscale;
+#pragma unroll
+        for (int j = 0; j < PZ; ++j) {
+            const int zo = zi - R + j;
+            if (zo < zb || zo >= ze) continue;
+            const int x = xt + 4 * n;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                const int x = xt + 16 * t + 4 * grp;
+                const int y = yt + wrow + 4 * t + grp;
                 if (y < g.ny && x < g.nx) {
                     float *po = g.out0 + (int64_t)zo * sz + (int64_t)y * sy + x;
-                    const floatx4 s = acc[0][t];
-                    const float4 o = make_float4(s[0] * outscale, s[1] * outscale,
-                                                 s[2] * outscale, s[3] * outscale);
+                    const floatx4 s = acc[j][t];
+                    const float4 o = PREC == MMS_FP16X3S
+                        ? make_float4(s[0] * od * oc, s[1] * od * oc, s[2] * od * oc, s[3] * od * oc)
+                        : make_float4(s[0], s[1], s[2], s[3]);
                     if (x + 3 < g.nx) {
                         *reinterpret_cast<float4 *>(po) = o;
                     } else {
@@ -330,15 +426,22 @@ __global__ void __launch_bounds__(64 * NW) box_mfma_kernel(MfmaArgs a) {
             }
         }
 #pragma unroll
-        for (int s = 0; s + 1 < Q; ++s)
+        for (int s = 0; s < NQ; ++s)
 #pragma unroll
-            for (int t = 0; t < NT; ++t) acc[s][t] = acc[s + 1][t];
+            for (int t = 0; t < NT; ++t)
+                acc[s][t] = s + PZ < NQ ? acc[s + PZ][t] : floatx4{0.f, 0.f, 0.f, 0.f};
+        if (PREC == MMS_FP16X3S && dnext != dscale) {
+            const float f = dnext / dscale;   // a power of two
 #pragma unroll
-        for (int t = 0; t < NT; ++t) acc[Q - 1][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int s = 0; s < NQ; ++s)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[s][t] *= f;
+            dscale = dnext;
+        }
         __syncthreads();   // every wave is done with plane zi
-        if (zi + 1 < z_last) {
-            write_plane();                              // plane zi + 1
-            if (zi + 2 < z_last) load_plane(zi + 2);    // requested a whole plane ahead
+        if (zi + PZ < z_last) {
+            write_plane();
+            if (zi + 2 * PZ < z_last) load_plane(zi + 2 * PZ);   // requested a whole step ahead
         }
         __syncthreads();
     }
@@ -347,8 +450,7 @@ __global__ void __launch_bounds__(64 * NW) box_mfma_kernel(MfmaArgs a) {
 template <int R, int PREC>
 int launch_rp(const float *in, float *out, const mms_grid *gd, const float *coeffs, hipStream_t s) {
     constexpr int Q = 2 * R + 1;
-    constexpr int NW = MCfg<R>::NW, NT = MCfg<R>::NT;
-    constexpr int BXT = 16 * NT, BYT = 16 * NW;
+    using S = Shape<R>;
     MfmaArgs a{};
     Geom &g = a.g;
     g.H = gd->halo;
@@ -359,12 +461,28 @@ int launch_rp(const float *in, float *out, const mms_grid *gd, const float *coef
     g.nz = (int)gd->nz;
     g.sy = gd->sy;
     g.sz = gd->sz;
-    g.ntx = (g.nx + BXT - 1) / BXT;
-    g.nty = (g.ny + BYT - 1) / BYT;
-    // one block per CU: about 256 blocks, chunks of at most 128 planes
+    g.ntx = (g.nx + S::BXT - 1) / S::BXT;
+    g.nty = (g.ny + S::BYT - 1) / S::BYT;
     const int64_t cols = (int64_t)g.ntx * g.nty;
-    int zc = (int)((int64_t)g.nz * cols / 256);
-    zc = zc < 32 ? 32 : (zc > 128 ? 128 : zc);
+    // z chunks: one block per CU at a time, so for each number of rounds the most chunks that
+    // fit it, and of those the choice with the fewest planes of work in a row.  A chunk reads
+    // zc + 2r planes in steps of PZ; the constant stands for a block's start (fragments, first
+    // loads), about four planes' time, and a quarter block for the uneven finish of a launch
+    // of several rounds.  (With chunks of at least 32 planes a 100^3 grid ran on 16 of the 256
+    // CUs: 297 us against 27.)
+    int zc = g.nz;
+    int64_t best = -1;
+    const int64_t k0 = (cols + 255) / 256;
+    for (int64_t k = k0; k < k0 + 16; ++k) {
+        const int64_t fit = 256 * k / cols;
+        const int nzc = (int)(fit < g.nz ? fit : g.nz), c = (g.nz + nzc - 1) / nzc;
+        const int64_t planes = (c + 2 * R + S::PZ - 1) / S::PZ * S::PZ + 4;
+        const int64_t cost = 4 * k * planes + (k > 1 ? planes : 0);
+        if (best < 0 || cost < best) {
+            best = cost;
+            zc = c;
+        }
+    }
     g.zchunk = zc;
     g.nzc = (g.nz + zc - 1) / zc;
     float cmax = 0.f;
@@ -381,7 +499,7 @@ int launch_rp(const float *in, float *out, const mms_grid *gd, const float *coef
     }
     const int64_t nblk = (int64_t)g.ntx * g.nty * g.nzc;
     if (nblk > 0x7fffffff) return MMS_EINVAL;
-    hipLaunchKernelGGL((box_mfma_kernel<R, PREC, NW, NT>), dim3((unsigned)nblk), dim3(64 * NW), 0,
+    hipLaunchKernelGGL((box_mfma_kernel<R, PREC>), dim3((unsigned)nblk), dim3(64 * S::NW), 0,
                        s, a);
     return check_launch("box_mfma_kernel");
 }
