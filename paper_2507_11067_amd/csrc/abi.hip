@@ -11,7 +11,8 @@
 
 namespace mms {
 
-int wave_step(const mms_wave *w, int n, const float *up, const float *uc, float *un, hipStream_t s);
+int wave_step(const mms_wave *w, int n, const float *up, const float *uc, float *un, int lag,
+              hipStream_t s);
 int wave_adjoint_step(const mms_wave *w, int n, const float *l2, const float *l1, float *l0,
                       const float *resid, const float *un, double *grad, hipStream_t s);
 int wave_record(const mms_wave *w, int n, const float *u, hipStream_t s);
@@ -194,7 +195,7 @@ int mms_wave_step(const mms_wave *w, int n, const float *u_prev, const float *u_
     if (overlap(u_cur, bytes, u_next, bytes)) return MMS_EINVAL;
     if (u_prev != u_next && overlap(u_prev, bytes, u_next, bytes)) return MMS_EINVAL;
     if (grid_empty(&w->g)) return MMS_OK;
-    return wave_step(w, n, u_prev, u_cur, u_next, (hipStream_t)stream);
+    return wave_step(w, n, u_prev, u_cur, u_next, 0, (hipStream_t)stream);
 }
 
 int mms_vti_step(const mms_wave *w, int n, const float *a, const float *b, const float *h_prev,
@@ -268,12 +269,30 @@ int mms_wave_forward(const mms_wave *w, int n_begin, int n_end, float *const *st
         const int i = n - n_begin;  // states[i] = u^{n-1}, states[i+1] = u^n, states[i+2] = u^{n+1}
         float *up = states[i], *uc = states[i + 1], *un = states[i + 2];
         if (!up || !uc || !un) return MMS_EINVAL;
+        if (!aligned16(up) || !aligned16(uc) || !aligned16(un)) return MMS_EINVAL;
         if (overlap(uc, bytes, un, bytes)) return MMS_EINVAL;
         if (up != un && overlap(up, bytes, un, bytes)) return MMS_EINVAL;
     }
+    if (grid_empty(&w->g)) return MMS_OK;
+    // Step n holds u^{n-1}, u^n and u^{n+1} in registers, so the image terms of three steps of
+    // this call are added together (oldest first, the sums of the steps one by one), at the
+    // third step, a block's last step or the call's: the block partial then crosses memory at
+    // 3 of 8 steps instead of all (400^3: 323 -> 258 us a step).
+    int pending = 0;
     for (int n = n_begin; n < n_end; ++n) {
         const int i = n - n_begin;
-        if (int rc = mms_wave_step(w, n, states[i], states[i + 1], states[i + 2], stream)) return rc;
+        const bool block_end = w->acc_block > 1 && ((n - 1) % w->acc_block == w->acc_block - 1 ||
+                                                    n == w->nt - 1);
+        int lag = -1;
+        if (pending == 2 || block_end || n + 1 == n_end) {
+            lag = pending;
+            pending = 0;
+        } else {
+            ++pending;
+        }
+        if (int rc = wave_step(w, n, states[i], states[i + 1], states[i + 2], lag,
+                               (hipStream_t)stream))
+            return rc;
     }
     return MMS_OK;
 }

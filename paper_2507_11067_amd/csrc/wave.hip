@@ -45,6 +45,8 @@ struct WaveArgs {
     float *part;          // FP32 partial of the current block (image or grad), or NULL
     int part_first;       // with part: first step of a block (part = term)
     int part_last;        // with part: last step of a block (acc64 += part + term)
+    int lag;              // FWD: levels before u^{n+1} whose terms this step adds too (0, 1: u^n,
+                          // 2: u^{n-1} and u^n)
     double *partials;     // ENERGY: one (FP64 partial, non-finite count) pair per block
     const float *src;     // device pointer to dt^2 f^n, or NULL
     int src_z, src_y, src_x;
@@ -53,6 +55,186 @@ struct WaveArgs {
     int faces;
     int mu_form;          // GRAD, first adjoint step: the adjoint variable is mu = C2 G lam
 };
+
+// s + v^2 with the square rounded first, so that a sum does not depend on which launches add
+// its terms.
+__device__ __forceinline__ float add_square(float s, float v) {
+#pragma clang fp contract(off)
+    const float t = v * v;
+    return s + t;
+}
+
+// The point-wise part of a pass at a lane's four cells (z, y, x0 ..): the update with the
+// sponge, source or receivers, its store, and the FP64 accumulations.  ctr and o: the stencil
+// field and S of it; pw0, pw1: the point-wise operands (see the modes in wave_kernel); off:
+// element offset of the cells within a plane; gown: the lane's sponge factors gy gx.
+template <int MODE>
+__device__ __forceinline__ void finish_cells(const WaveArgs &a, int z, int y, int x0, int64_t off,
+                                             bool live, float gz, const float *gown,
+                                             const float4 &ctr, const float *o, const float4 &pw0,
+                                             const float4 &pw1, float srcv, double &esum,
+                                             double &ebad) {
+    const Geom &g = a.g;
+    const int64_t sz = g.sz;
+    const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
+    const int64_t dense = ((int64_t)z * g.ny + y) * g.nx + x0;
+    float *po = a.out ? a.out + (int64_t)z * sz + off : nullptr;
+    const float p0v[4] = {pw0.x, pw0.y, pw0.z, pw0.w};
+    const float p1v[4] = {pw1.x, pw1.y, pw1.z, pw1.w};
+    const float cv[4] = {ctr.x, ctr.y, ctr.z, ctr.w};
+    float r[4] = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (MODE == MODE_FWD || MODE == MODE_ADJMU) {
+        // FWD: p0 = u^{n-1}, p1 = C2, ctr = u^n; ADJMU: p0 = mu^{n+2}, ctr = mu^{n+1}
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float G = gz * gown[e];
+            r[e] = G * (2.0f * cv[e] - G * p0v[e] + a.c2s * p1v[e] * o[e]);
+        }
+        if constexpr (MODE == MODE_FWD) {
+            if (srcv != 0.f && z == a.src_z && y == a.src_y && a.src_x >= x0 &&
+                a.src_x < x0 + 4) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (x0 + e == a.src_x) r[e] += srcv;
+            }
+        } else {
+            // receivers: + C2 G r^n on the plane z = 0
+            if (a.resid && z == 0 && live) {
+                const float *rs = a.resid + (int64_t)y * g.nx + x0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (x0 + e < g.nx) r[e] += a.c2s * p1v[e] * (gz * gown[e]) * rs[e];
+            }
+        }
+    } else if constexpr (MODE == MODE_ADJ) {
+        // p0 = lam^{n+2}, p1 = lam^{n+1}
+        const float *rs = (a.resid && z == 0) ? a.resid + (int64_t)y * g.nx + x0 : nullptr;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float G = gz * gown[e];
+            r[e] = 2.0f * G * p1v[e] - G * G * p0v[e] + o[e];
+            if (rs && live && x0 + e < g.nx) r[e] += rs[e];
+        }
+    } else if constexpr (MODE == MODE_ENERGY) {
+        // ENERGY: p0 = u^{n+1}, p1 = C2, ctr = u^n, o = S u^n
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (live && x0 + e < g.nx) {
+                const double d = (double)p0v[e] - (double)cv[e];
+                double t = -(double)p0v[e] * (double)o[e];
+                if (p1v[e] != 0.f) t += d * d / ((double)a.c2s * (double)p1v[e]);
+                esum += t;
+                ebad += isfinite(t) ? 0.0 : 1.0;
+            }
+        }
+    }
+    if (MODE != MODE_ENERGY && live) {
+        if (MODE == MODE_GRAD) {
+            // no field output
+        } else if (x0 + 3 < g.nx) {
+            // streaming store: the next step reads this field from HBM anyway
+            const f4v v = {r[0], r[1], r[2], r[3]};
+            __builtin_nontemporal_store(v, reinterpret_cast<f4v *>(po));
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (x0 + e < g.nx) po[e] = r[e];
+        }
+        if (MODE == MODE_FWD && a.traces && z == 0) {
+            float *pt = a.traces + (int64_t)y * g.nx + x0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (x0 + e < g.nx) pt[e] = cv[e];
+        }
+        if (MODE == MODE_FWD || MODE == MODE_GRAD) if (a.acc64) {
+            // the accumulated term of each cell: FWD (u^{n+1})^2 (and of up to two levels
+            // before it, oldest first), GRAD G lam^{n+1} S(u^n) (p0 = lam^{n+1}, o = S u^n); in
+            // FP32 for the block partial, in FP64 for a direct update (add64)
+            float t[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                t[e] = a.mu_form ? p0v[e] * o[e]      // mu^{n+1} S(u^n), / c2 below
+                                 : a.c2s * gz * gown[e] * p0v[e] * o[e];
+            // mu form: c2 G lam^{n+1} S(u^n) = mu^{n+1} S(u^n) / c2, with c2 the field
+            // (C2 = c2s c2); the division is done in FP64 where a sum reaches acc64,
+            // so the c2 field is read (cell by cell) once per block of steps
+            const bool div_c2 = MODE == MODE_GRAD && a.mu_form;
+            const float *c2row = a.c2 + (int64_t)z * sz + off;
+            auto fin = [&](int e, double v) -> double {
+                return div_c2 ? v / (double)c2row[e] : v;
+            };
+            auto add64 = [&](int e, double v) -> double {
+                if constexpr (MODE == MODE_GRAD) return v + fin(e, (double)t[e]);
+                if (a.lag == 2) v += (double)p0v[e] * (double)p0v[e];
+                if (a.lag >= 1) v += (double)cv[e] * (double)cv[e];
+                return v + (double)r[e] * (double)r[e];
+            };
+            auto add32 = [&](int e, float v) -> float {
+                if constexpr (MODE == MODE_GRAD) return a.part_first ? t[e] : v + t[e];
+                v = a.part_first ? 0.f : v;
+                if (a.lag == 2) v = add_square(v, p0v[e]);
+                if (a.lag >= 1) v = add_square(v, cv[e]);
+                return add_square(v, r[e]);
+            };
+            double *pa = a.acc64 + dense;
+            // four cells in range on a 16-byte aligned dense row: one 16-byte
+            // access per operand (two for the FP64 sums) instead of four
+            const bool vec = x0 + 3 < g.nx && (dense & 3) == 0;
+            if (!a.part) {
+                if (vec) {
+                    double2 *p2 = reinterpret_cast<double2 *>(pa);
+                    double2 lo = p2[0], hi = p2[1];
+                    lo.x = add64(0, lo.x);
+                    lo.y = add64(1, lo.y);
+                    hi.x = add64(2, hi.x);
+                    hi.y = add64(3, hi.y);
+                    p2[0] = lo;
+                    p2[1] = hi;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (x0 + e < g.nx) pa[e] = add64(e, pa[e]);
+                }
+            } else {
+                // FP32 partial over the block, added in FP64 at its end
+                float *pp = a.part + dense;
+                if (vec) {
+                    // GRAD: the partial came with the point-wise operands
+                    const float4 pv = a.part_first ? zero4
+                                      : MODE == MODE_GRAD ? pw1
+                                                          : *reinterpret_cast<const float4 *>(pp);
+                    const float pa4[4] = {pv.x, pv.y, pv.z, pv.w};
+                    float sum[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum[e] = add32(e, pa4[e]);
+                    if (a.part_last) {
+                        double2 *p2 = reinterpret_cast<double2 *>(pa);
+                        double2 lo = p2[0], hi = p2[1];
+                        lo.x += fin(0, (double)sum[0]);
+                        lo.y += fin(1, (double)sum[1]);
+                        hi.x += fin(2, (double)sum[2]);
+                        hi.y += fin(3, (double)sum[3]);
+                        p2[0] = lo;
+                        p2[1] = hi;
+                    } else {
+                        *reinterpret_cast<float4 *>(pp) = make_float4(sum[0], sum[1], sum[2], sum[3]);
+                    }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if (x0 + e < g.nx) {
+                            const float sum = add32(e, a.part_first ? 0.f : pp[e]);
+                            if (a.part_last)
+                                pa[e] += fin(e, (double)sum);
+                            else
+                                pp[e] = sum;
+                        }
+                    }
+                }
+            }
+        }
+    }
+}
 
 template <int R, int MODE, int TX, int TY>
 __global__ void __launch_bounds__(TX *TY) wave_kernel(WaveArgs a) {
@@ -241,154 +423,8 @@ __global__ void __launch_bounds__(TX *TY) wave_kernel(WaveArgs a) {
                 }
                 const float gz = gaxis(z, g.nz, W, sa, zlo, zhi);
                 const bool live = lane_on && y < g.ny && x0 < g.nx;
-                const int64_t dense = ((int64_t)z * g.ny + y) * g.nx + x0;
-                float *po = a.out ? a.out + (int64_t)z * sz + own_off : nullptr;
-                const float p0v[4] = {pw0.x, pw0.y, pw0.z, pw0.w};
-                const float p1v[4] = {pw1.x, pw1.y, pw1.z, pw1.w};
-                const float cv[4] = {ctr.x, ctr.y, ctr.z, ctr.w};
-                float r[4] = {0.f, 0.f, 0.f, 0.f};
-                if constexpr (MODE == MODE_FWD || MODE == MODE_ADJMU) {
-                    // FWD: p0 = u^{n-1}, p1 = C2, ctr = u^n; ADJMU: p0 = mu^{n+2}, ctr = mu^{n+1}
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float G = gz * gown[e];
-                        r[e] = G * (2.0f * cv[e] - G * p0v[e] + a.c2s * p1v[e] * o[e]);
-                    }
-                    if constexpr (MODE == MODE_FWD) {
-                        if (srcv != 0.f && z == a.src_z && y == a.src_y && a.src_x >= x0 &&
-                            a.src_x < x0 + 4) {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                if (x0 + e == a.src_x) r[e] += srcv;
-                        }
-                    } else {
-                        // receivers: + C2 G r^n on the plane z = 0
-                        if (a.resid && z == 0 && live) {
-                            const float *rs = a.resid + (int64_t)y * g.nx + x0;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                if (x0 + e < g.nx) r[e] += a.c2s * p1v[e] * (gz * gown[e]) * rs[e];
-                        }
-                    }
-                } else if constexpr (MODE == MODE_ADJ) {
-                    // p0 = lam^{n+2}, p1 = lam^{n+1}
-                    const float *rs = (a.resid && z == 0) ? a.resid + (int64_t)y * g.nx + x0 : nullptr;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float G = gz * gown[e];
-                        r[e] = 2.0f * G * p1v[e] - G * G * p0v[e] + o[e];
-                        if (rs && live && x0 + e < g.nx) r[e] += rs[e];
-                    }
-                } else if constexpr (MODE == MODE_ENERGY) {
-                    // ENERGY: p0 = u^{n+1}, p1 = C2, ctr = u^n, o = S u^n
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if (live && x0 + e < g.nx) {
-                            const double d = (double)p0v[e] - (double)cv[e];
-                            double t = -(double)p0v[e] * (double)o[e];
-                            if (p1v[e] != 0.f) t += d * d / ((double)a.c2s * (double)p1v[e]);
-                            esum += t;
-                            ebad += isfinite(t) ? 0.0 : 1.0;
-                        }
-                    }
-                }
-                if (MODE != MODE_ENERGY && live) {
-                    if (MODE == MODE_GRAD) {
-                        // no field output
-                    } else if (x0 + 3 < g.nx) {
-                        // streaming store: the next step reads this field from HBM anyway
-                        const f4v v = {r[0], r[1], r[2], r[3]};
-                        __builtin_nontemporal_store(v, reinterpret_cast<f4v *>(po));
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (x0 + e < g.nx) po[e] = r[e];
-                    }
-                    if (MODE == MODE_FWD && a.traces && z == 0) {
-                        float *pt = a.traces + (int64_t)y * g.nx + x0;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (x0 + e < g.nx) pt[e] = cv[e];
-                    }
-                    if (MODE == MODE_FWD || MODE == MODE_GRAD) if (a.acc64) {
-                        // the accumulated term of each cell: FWD (u^{n+1})^2, GRAD
-                        // G lam^{n+1} S(u^n) (p0 = lam^{n+1}, o = S u^n); in FP32 for the
-                        // block partial, in FP64 for a direct update (t64)
-                        float t[4];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            t[e] = MODE == MODE_FWD ? r[e] * r[e]
-                                   : a.mu_form ? p0v[e] * o[e]      // mu^{n+1} S(u^n), / c2 below
-                                               : a.c2s * gz * gown[e] * p0v[e] * o[e];
-                        // mu form: c2 G lam^{n+1} S(u^n) = mu^{n+1} S(u^n) / c2, with c2 the field
-                        // (C2 = c2s c2); the division is done in FP64 where a sum reaches acc64,
-                        // so the c2 field is read (cell by cell) once per block of steps
-                        const bool div_c2 = MODE == MODE_GRAD && a.mu_form;
-                        const float *c2row = a.c2 + (int64_t)z * sz + own_off;
-                        auto fin = [&](int e, double v) -> double {
-                            return div_c2 ? v / (double)c2row[e] : v;
-                        };
-                        auto t64 = [&](int e) -> double {
-                            return MODE == MODE_FWD ? (double)r[e] * (double)r[e] : fin(e, (double)t[e]);
-                        };
-                        double *pa = a.acc64 + dense;
-                        // four cells in range on a 16-byte aligned dense row: one 16-byte
-                        // access per operand (two for the FP64 sums) instead of four
-                        const bool vec = x0 + 3 < g.nx && (dense & 3) == 0;
-                        if (!a.part) {
-                            if (vec) {
-                                double2 *p2 = reinterpret_cast<double2 *>(pa);
-                                double2 lo = p2[0], hi = p2[1];
-                                lo.x += t64(0);
-                                lo.y += t64(1);
-                                hi.x += t64(2);
-                                hi.y += t64(3);
-                                p2[0] = lo;
-                                p2[1] = hi;
-                            } else {
-#pragma unroll
-                                for (int e = 0; e < 4; ++e)
-                                    if (x0 + e < g.nx) pa[e] += t64(e);
-                            }
-                        } else {
-                            // FP32 partial over the block, added in FP64 at its end
-                            float *pp = a.part + dense;
-                            if (vec) {
-                                // GRAD: the partial came with the point-wise operands
-                                const float4 pv = a.part_first ? zero4
-                                                  : MODE == MODE_GRAD ? pw1
-                                                                      : *reinterpret_cast<const float4 *>(pp);
-                                const float pa4[4] = {pv.x, pv.y, pv.z, pv.w};
-                                float sum[4];
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) sum[e] = a.part_first ? t[e] : pa4[e] + t[e];
-                                if (a.part_last) {
-                                    double2 *p2 = reinterpret_cast<double2 *>(pa);
-                                    double2 lo = p2[0], hi = p2[1];
-                                    lo.x += fin(0, (double)sum[0]);
-                                    lo.y += fin(1, (double)sum[1]);
-                                    hi.x += fin(2, (double)sum[2]);
-                                    hi.y += fin(3, (double)sum[3]);
-                                    p2[0] = lo;
-                                    p2[1] = hi;
-                                } else {
-                                    *reinterpret_cast<float4 *>(pp) = make_float4(sum[0], sum[1], sum[2], sum[3]);
-                                }
-                            } else {
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) {
-                                    if (x0 + e < g.nx) {
-                                        const float sum = a.part_first ? t[e] : pp[e] + t[e];
-                                        if (a.part_last)
-                                            pa[e] += fin(e, (double)sum);
-                                        else
-                                            pp[e] = sum;
-                                    }
-                                }
-                            }
-                        }
-                    }
-                }
+                finish_cells<MODE>(a, z, y, x0, own_off, live, gz, gown, ctr, o, pw0, pw1, srcv, esum,
+                                   ebad);
                 if (more) {
                     ring_store((z + R + 1) % NR, nq, hreg);
                     q[ph] = nq;
@@ -528,18 +564,22 @@ int launch_mode(WaveArgs &a, const mms_grid *gd, int r, hipStream_t s) {
 
 }  // namespace
 
-int wave_step(const mms_wave *w, int n, const float *up, const float *uc, float *un, hipStream_t s) {
+// lag: terms of earlier levels that the step adds to the image with its own (0 to 2), or -1 to
+// leave the image to a later step of the same call
+int wave_step(const mms_wave *w, int n, const float *up, const float *uc, float *un, int lag,
+              hipStream_t s) {
     WaveArgs a = base_args(w);
     const int64_t o = (int64_t)w->g.halo * (w->g.sz + w->g.sy + 1);
     a.f0 = uc + o;
     a.p0 = up + o;
     a.out = un + o;
     a.traces = w->traces ? w->traces + (int64_t)n * w->g.ny * w->g.nx : nullptr;
-    a.acc64 = w->image;
-    if (w->image && w->acc_block > 1) {
+    a.acc64 = lag >= 0 ? w->image : nullptr;
+    a.lag = lag;
+    if (a.acc64 && w->acc_block > 1) {
         const int K = w->acc_block, ph = (n - 1) % K;
         a.part = w->acc_part;
-        a.part_first = ph == 0;
+        a.part_first = ph == lag;
         a.part_last = ph == K - 1 || n == w->nt - 1;
     }
     a.src = (w->src_dt2f && n >= 0 && n < w->nt) ? w->src_dt2f + n : nullptr;
