@@ -460,6 +460,58 @@ __global__ void __launch_bounds__(TX *TY) wave_kernel(WaveArgs a) {
     }
 }
 
+// Small grids: one lane per 16-byte word reads its 4r + 3 words of the stencil field straight
+// from memory (the operations, and their order, are those of wave_kernel).
+template <int R, int MODE>
+__global__ void __launch_bounds__(256) wave_direct_kernel(WaveArgs a, unsigned nwords, unsigned nxw) {
+    const unsigned i = (unsigned)mms_xcd_remap(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
+    if (i >= nwords) return;
+    const Geom &g = a.g;
+    const unsigned row = i / nxw;
+    const int x0 = 4 * (int)(i % nxw), y = (int)(row % (unsigned)g.ny), z = (int)(row / (unsigned)g.ny);
+    const int64_t off = (int64_t)y * g.sy + x0;
+    const int64_t zoff = (int64_t)z * g.sz + off;
+    auto ld = [](const float *q) { return *reinterpret_cast<const float4 *>(q); };
+    const float *p = a.f0 + zoff;
+    const float4 L = ld(p - 4), ctr = ld(p), Rr = ld(p + 4);
+    float4 vy[2 * R + 1], vz[2 * R + 1];
+#pragma unroll
+    for (int k = -R; k <= R; ++k) {
+        vy[k + R] = k == 0 ? ctr : ld(p + k * g.sy);
+        vz[k + R] = k == 0 ? ctr : ld(p + k * g.sz);
+    }
+    const int64_t dense = ((int64_t)z * g.ny + y) * g.nx + x0;
+    const bool part = MODE == MODE_GRAD && a.part && !a.part_first && x0 + 3 < g.nx && (dense & 3) == 0;
+    const float4 pw0 = ld(a.p0 + zoff);
+    const float4 pw1 = MODE != MODE_GRAD ? ld(a.c2 + zoff) : ld(part ? a.part + dense : a.c2);
+    const float srcv = (MODE == MODE_FWD && a.src) ? *a.src : 0.f;
+    const int W = a.sponge_w;
+    const float sa = a.sponge_a;
+    float gown[4];
+    const float gy = gaxis(y, g.ny, W, sa, a.faces & 4, a.faces & 8);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) gown[e] = gy * gaxis(x0 + e, g.nx, W, sa, a.faces & 1, a.faces & 2);
+    const float gz = gaxis(z, g.nz, W, sa, a.faces & 16, a.faces & 32);
+    const float *c = a.c;
+    float o[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = -R; k <= R; ++k) {
+        const float ck = c[R + k];
+        o[0] = fmaf(ck, vz[R + k].x + vy[R + k].x, o[0]);
+        o[1] = fmaf(ck, vz[R + k].y + vy[R + k].y, o[1]);
+        o[2] = fmaf(ck, vz[R + k].z + vy[R + k].z, o[2]);
+        o[3] = fmaf(ck, vz[R + k].w + vy[R + k].w, o[3]);
+    }
+    const float w[12] = {L.x,   L.y,   L.z,   L.w,  ctr.x, ctr.y,
+                         ctr.z, ctr.w, Rr.x, Rr.y, Rr.z,  Rr.w};
+#pragma unroll
+    for (int k = -R; k <= R; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = fmaf(c[R + k], w[4 + e + k], o[e]);
+    double esum = 0.0, ebad = 0.0;
+    finish_cells<MODE>(a, z, y, x0, off, true, gz, gown, ctr, o, pw0, pw1, srcv, esum, ebad);
+}
+
 // lam^0 = -G^2 lam^2 + R^T r^0 (point-wise; u^0 enters only through step 1's G^2 term)
 __global__ void adjoint_first_kernel(WaveArgs a) {
     const Geom &g = a.g;
@@ -517,6 +569,12 @@ __global__ void record_kernel(const float *u0, float *tr, int nx, int ny, int64_
 // Tile shape: up to 256 x 16 cells per block (64 x 16 lanes); the LDS ring fills most
 // of a CU's LDS, so one block runs per CU.
 constexpr int WTX = 64, WTY = 16;
+// Grids of at most this many points take the direct kernel (one lane per word, no LDS, no
+// barriers): a marching block walks its chunk at about a memory latency per plane, 16-18 us a
+// step however small the grid is, where the direct reads go through L2 4r + 3 times.  Radius 4,
+// us a step, direct / marching: 5.4 / 16.2 at 64^3, 6.3 / 16.6 at 96^3, 11.1 / 17.7 at 128^3,
+// 19.0 / 19.0 at 160^3, 33.9 / 27.9 at 200^3 (radius 2: 15.4 / 16.8 and 26.8 / 26.5).
+constexpr int64_t DIRECT_MAX = (int64_t)7 << 19;   // 3.67 M points
 
 void fill_geom(Geom &g, const mms_grid *gd) {
     g.H = gd->halo;
@@ -551,6 +609,21 @@ int launch_mode(WaveArgs &a, const mms_grid *gd, int r, hipStream_t s) {
     fill_geom(a.g, gd);
     const int64_t nblk = (int64_t)a.g.ntx * a.g.nty * a.g.nzc;
     if (nblk > 0x7fffffff) return MMS_EINVAL;
+    if constexpr (MODE == MODE_FWD || MODE == MODE_ADJMU || MODE == MODE_GRAD) {
+        if ((int64_t)a.g.nx * a.g.ny * a.g.nz <= DIRECT_MAX) {
+            const unsigned nxw = (unsigned)(a.g.nx + 3) / 4;
+            const unsigned nwords = nxw * (unsigned)a.g.ny * (unsigned)a.g.nz;
+            const dim3 grid((nwords + 255) / 256), block(256);
+            switch (r) {
+                case 1: hipLaunchKernelGGL((wave_direct_kernel<1, MODE>), grid, block, 0, s, a, nwords, nxw); break;
+                case 2: hipLaunchKernelGGL((wave_direct_kernel<2, MODE>), grid, block, 0, s, a, nwords, nxw); break;
+                case 3: hipLaunchKernelGGL((wave_direct_kernel<3, MODE>), grid, block, 0, s, a, nwords, nxw); break;
+                case 4: hipLaunchKernelGGL((wave_direct_kernel<4, MODE>), grid, block, 0, s, a, nwords, nxw); break;
+                default: return MMS_EUNSUPPORTED;
+            }
+            return check_launch("wave_direct_kernel");
+        }
+    }
     const dim3 grid((unsigned)nblk), block(TX * TY);
     switch (r) {
         case 1: hipLaunchKernelGGL((wave_kernel<1, MODE, TX, TY>), grid, block, 0, s, a); break;
