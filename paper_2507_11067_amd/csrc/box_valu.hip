@@ -319,13 +319,13 @@ int launch_r(const float *in, float *out, const mms_grid *gd, const float *coeff
     g.ntx = (g.nx + 4 * TX - 1) / (4 * TX);
     g.nty = (g.ny + TY * NYL - 1) / (TY * NYL);
     const int64_t cols = (int64_t)g.ntx * g.nty;
-    // about 4096 blocks of one output row per lane (2048 of two); a round model of the
-    // resident blocks (as in the 2-D sweeps) measured no faster at 512^3
-    int zc = (int)((int64_t)g.nz * cols * NYL / 4096);
-    zc = zc < 16 ? 16 : zc;
-    // radius 1 is bound by HBM: long chunks cut the re-read halo planes
-    // (measured at 512^3: 512 Gpoints/s at 128 planes against 441 at 32)
-    if (R == 1) zc = 128;
+    // z chunks by rounds over the resident blocks: four 256-thread blocks per CU from radius 2
+    // on, one of 1024 threads at radius 1.  A chunk's 2r halo planes feed about half their
+    // outputs, so four planes stand for them and the block's start.  (With chunks of at least
+    // 16 planes, 128 at radius 1, small grids left most CUs idle: 100^3 at radius 1 / 2 / 3 / 4
+    // took 163 / 53 / 143 / 253 us against 12 / 13 / 46 / 46; at 512^3 the chunk lengths, and
+    // the times, stay as they were.)
+    const int zc = pick_zchunk_rounds(g.nz, cols, R == 1 ? 256 : 1024, 1, 128, 4);
     g.zchunk = zc;
     g.nzc = (g.nz + zc - 1) / zc;
     for (int i = 0; i < W * W * W; ++i) a.c[i] = coeffs[i];
