@@ -12,6 +12,7 @@ from __future__ import annotations
 import ctypes
 from dataclasses import dataclass
 
+import numpy as np
 import torch
 
 from . import _lib
@@ -82,8 +83,19 @@ class Grid:
 
 def _stream(stream) -> ctypes.c_void_p:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the current stream's handle without the Stream object around it (2.7 us a call)
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return ctypes.c_void_p(stream.cuda_stream)
+
+
+def _floats(coeffs):
+    """(pointer to contiguous FP32 host values, their number, the object that holds them).  An
+    FP32 C-contiguous numpy array is passed as it is: the way through torch costs 2 us a call."""
+    if type(coeffs) is np.ndarray and coeffs.dtype == np.float32 and coeffs.flags.c_contiguous:
+        n, addr = coeffs.size, coeffs.__array_interface__["data"][0]
+        return (ctypes.c_float * n).from_address(addr), n, coeffs
+    c = torch.as_tensor(coeffs, dtype=torch.float32).detach().cpu().contiguous().reshape(-1)
+    return ctypes.cast(c.data_ptr(), ctypes.POINTER(ctypes.c_float)), c.numel(), c
 
 
 def _grid_ptr(t: torch.Tensor | None, grid: Grid, name: str, dtype=torch.float32):
@@ -91,7 +103,7 @@ def _grid_ptr(t: torch.Tensor | None, grid: Grid, name: str, dtype=torch.float32
         return None
     if not t.is_cuda or t.dtype != dtype or not t.is_contiguous():
         raise ValueError(f"{name}: need a contiguous {dtype} CUDA tensor")
-    if tuple(t.shape) != grid.shape:
+    if t.shape != grid.shape:
         raise ValueError(f"{name}: shape {tuple(t.shape)} does not match grid {grid.shape}")
     return ctypes.c_void_p(t.data_ptr())
 
@@ -109,12 +121,11 @@ def _dev_ptr(t: torch.Tensor | None, name: str, dtype, numel: int | None = None)
 def stencil_apply(inp: torch.Tensor, out: torch.Tensor, grid: Grid, shape: str, radius: int,
                   coeffs, precision: str = "fp32", stream=None) -> torch.Tensor:
     """One sweep out = S(inp) (star, box, star2d or box2d, radius 1..4), see mms_stencil_apply."""
-    c = torch.as_tensor(coeffs, dtype=torch.float32).detach().cpu().contiguous().reshape(-1)
+    c, n, hold = _floats(coeffs)
     g = grid.c()
     rc = lib().mms_stencil_apply(_grid_ptr(inp, grid, "inp"), _grid_ptr(out, grid, "out"),
                                  ctypes.byref(g), SHAPES[shape], int(radius),
-                                 ctypes.cast(c.data_ptr(), ctypes.POINTER(ctypes.c_float)),
-                                 c.numel(), PRECISIONS[precision], _stream(stream))
+                                 c, n, PRECISIONS[precision], _stream(stream))
     check(rc, "mms_stencil_apply")
     return out
 
