@@ -13,9 +13,9 @@ WavePropagate.apply(m, u0, u1, problem) -> traces [nt, ny, nx]
 
 Memory plan: the forward pass keeps the pair (u^k, u^{k+1}) at every level
 k = 0, K, 2K, ... .  The backward pass walks the segments [k, k+K) from the
-last to the first: it restores the pair, recomputes u^{k+2} .. u^{k+K-1} into
-a K-level buffer, then runs the adjoint steps k+K-1 .. k, which read u^n from
-that buffer and accumulate the FP64 gradient.  Extra cost: one more forward
+last to the first: it recomputes u^{k+2} .. u^{k+K-1} from the pair into K - 2
+buffers, then runs the adjoint steps k+K-1 .. k, which read u^n from the pair
+and those buffers and accumulate the FP64 gradient.  Extra cost: one more forward
 sweep; extra memory: 2 nt/K + K grids.  With Problem.store_all the forward
 pass writes every level into a grid of its own instead (nt + 1 grids, 74 GB
 for 256^3 x 1000 steps, within one MI355X's 288 GB) and the backward pass
@@ -87,7 +87,9 @@ class WavePropagate(torch.autograd.Function):
             if nt > 0:
                 w.record(0, bufs[0])
             for k in range(0, nt, K):
-                ckpts.append((bufs[k % 3].clone(), bufs[(k + 1) % 3].clone()))
+                # (the last pair feeds no later step and is kept without a copy)
+                pair = bufs[k % 3], bufs[(k + 1) % 3]
+                ckpts.append(pair if k + 1 == nt else tuple(b.clone() for b in pair))
                 n_end = min(k + K + 1, nt)
                 if n_end > k + 1:
                     w.forward(k + 1, n_end, [bufs[(k + i) % 3] for i in range(n_end - k + 1)])
@@ -117,8 +119,12 @@ class WavePropagate(torch.autograd.Function):
         else:
             mu_form = prob.adjoint_form == "mu"
         adjoint = wa.adjoint_mu if mu_form else wa.adjoint
-        lam = [g.zeros(dev) for _ in range(3)]   # lam^n (or mu^n) lives in lam[n % 3]
-        seg = [] if ctx.levels is not None else [g.zeros(dev) for _ in range(min(K, max(nt, 1)))]
+        # lam^n (or mu^n) lives in lam[n % 2]: a step writes it over lam^{n+2}, which it reads
+        # cell by cell (256^3: 45 us a step in place, 50 with three buffers, whose fourth field
+        # no longer fits the 256 MB cache beside C2)
+        lam = [g.zeros(dev) for _ in range(2)]
+        # levels k+2 .. of a segment; its first two are the checkpoint itself
+        seg = [] if ctx.levels is not None else [g.zeros(dev) for _ in range(min(K, max(nt, 1)) - 2)]
         grad = torch.zeros((g.nz, g.ny, g.nx), dtype=torch.float64, device=dev)
         if prob.grad_block > 1:
             # each block of grad_block adjoint steps is summed in FP32, then added in FP64
@@ -127,25 +133,23 @@ class WavePropagate(torch.autograd.Function):
         w_src = prob.wave(m)               # recompute: same source, no receivers
         if ctx.levels is not None and nt > 0:
             # every level is resident: the whole adjoint in one call
-            adjoint(nt - 1, 0, [lam[i % 3] for i in range(nt + 2)], us=ctx.levels[0:nt],
+            adjoint(nt - 1, 0, [lam[i % 2] for i in range(nt + 2)], us=ctx.levels[0:nt],
                     resid=resid, grad=grad)
         for si in range(len(ctx.ckpts) - 1, -1, -1):
             k = si * K
             hi = min(k + K, nt) - 1
-            seg[0].copy_(ctx.ckpts[si][0])
-            if hi >= k + 1:
-                seg[1].copy_(ctx.ckpts[si][1])
+            us = (list(ctx.ckpts[si]) + seg)[0:hi - k + 1]   # u^k .. u^hi
             if hi >= k + 2:
-                w_src.forward(k + 1, hi, seg[0:hi - k + 1])
+                w_src.forward(k + 1, hi, us)
                 recomputed += hi - k - 1
-            adjoint(hi, k, [lam[(k + i) % 3] for i in range(hi - k + 3)],
-                    us=seg[0:hi - k + 1], resid=resid, grad=grad)
+            adjoint(hi, k, [lam[(k + i) % 2] for i in range(hi - k + 3)],
+                    us=us, resid=resid, grad=grad)
         if mu_form:
-            for b in lam[:2]:
+            for b in lam:
                 wa.scale_mu(b, b, -1)      # mu^0, mu^1 -> lam^0, lam^1
         grad_m = dense_to_grid(grad, g.zeros(dev), g)
-        grad_u0 = lam[0].clone() if nt > 0 else g.zeros(dev)
-        grad_u1 = lam[1 % 3].clone() if nt > 1 else g.zeros(dev)
+        grad_u0 = lam[0] if nt > 0 else g.zeros(dev)
+        grad_u1 = lam[1] if nt > 1 else g.zeros(dev)
         prob.stats["recomputed_steps"] = recomputed
         ctx.levels = None
         prob.stats["adjoint_form"] = "mu" if mu_form else "lam"
