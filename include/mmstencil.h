@@ -222,7 +222,8 @@ typedef struct mms_tti {
     float d1[4];               /* first-derivative weights d_1..d_radius:                   */
                                /* D f(i) = sum_k d_k (f(i+k) - f(i-k))                       */
     float *work;               /* device workspace of 4 grids (layout g, 16-byte aligned),  */
-                               /* overwritten by every call; caller-owned                   */
+                               /* caller-owned; a call may overwrite it (the present kernel */
+                               /* keeps its intermediate derivatives on chip)               */
 } mms_tti;
 
 /*
@@ -237,9 +238,8 @@ typedef struct mms_tti {
  * first-derivative stencil t->d1 along the two axes (the composition of one-dimensional
  * stencils of Sec. IV-G).  traces[n] = p^n(z = 0); the image is not used.  Grid cells are read
  * as stored, halo included.  p_next may equal p_prev and q_next may equal q_prev; no other
- * pair of arguments (work included) may overlap.  The second pass addresses tiles of
- * (8 + 2r + 1) rows with 32-bit offsets: a pitch sy with (9 + 2r) * sy >= 2^32 gives
- * MMS_EUNSUPPORTED before either pass runs.
+ * pair of arguments (work included) may overlap.  A pitch sy with (9 + 2r) * sy >= 2^32 gives
+ * MMS_EUNSUPPORTED.
  */
 int mms_tti_step(const mms_wave *w, const mms_tti *t, int n, const float *p_prev,
                  const float *p_cur, float *p_next, const float *q_prev, const float *q_cur,

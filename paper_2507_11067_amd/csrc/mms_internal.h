@@ -67,22 +67,31 @@ inline int pick_zchunk(int nz, int64_t cols, int64_t slots, int zmin, int zmax) 
 // z-chunk that minimises the modelled time of a launch whose blocks all take about
 // the same time: ceil(blocks / slots) rounds of (zchunk + overhead) planes, where
 // overhead is the per-block fill of the z pipeline in planes, plus a quarter block
-// for the uneven finish of the last round.  Larger chunks win ties.
+// for the uneven finish of the last round.  For each number of rounds only the most
+// chunks that fit it can win, so the rounds are walked, not the chunk lengths (a hundred
+// and more on each call), until their overhead alone costs more than the best.
 inline int pick_zchunk_rounds(int nz, int64_t cols, int64_t slots, int zmin, int zmax,
-                              int overhead) {
+                              int overhead, int64_t *cost_out = nullptr) {
     if (cols < 1) cols = 1;
     if (zmax > nz) zmax = nz > zmin ? nz : zmin;
     int best = zmax;
     int64_t best_cost = -1;
-    for (int zc = zmax; zc >= zmin; --zc) {
-        const int64_t nzc = (nz + zc - 1) / zc;
-        const int64_t rounds = (cols * nzc + slots - 1) / slots;
+    const int64_t k0 = (cols * ((nz + zmax - 1) / zmax) + slots - 1) / slots;
+    const int64_t floor4 = 4 * (nz * cols / slots);
+    for (int64_t k = k0; best_cost < 0 || floor4 + 4 * k * overhead <= best_cost; ++k) {
+        const int64_t fit = slots * k / cols;
+        const int nzc = (int)(fit < nz ? fit : nz);
+        int zc = (nz + nzc - 1) / nzc;
+        zc = zc < zmin ? zmin : zc > zmax ? zmax : zc;
+        const int64_t rounds = (cols * ((nz + zc - 1) / zc) + slots - 1) / slots;
         const int64_t cost4 = 4 * rounds * (int64_t)(zc + overhead) + zc;  // quarter planes
         if (best_cost < 0 || cost4 < best_cost) {
             best_cost = cost4;
             best = zc;
         }
+        if (zc == zmin) break;
     }
+    if (cost_out) *cost_out = best_cost;
     return best;
 }
 
