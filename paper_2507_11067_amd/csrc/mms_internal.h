@@ -31,6 +31,7 @@ struct Geom {
     int ntx, nty, nzc;  // tile counts along x, y and z chunks
     int zchunk;
     int txa;            // kernels with balanced x tiles: active lanes per tile row
+    int rows;           // kernels with flat tiles: rows of a tile
 };
 
 // Balanced x tiles: the fewest tiles of at most `lanes` 16-byte words that cover
@@ -93,6 +94,40 @@ inline int pick_zchunk_rounds(int nz, int64_t cols, int64_t slots, int zmin, int
     }
     if (cost_out) *cost_out = best_cost;
     return best;
+}
+
+// Wave and VTI steps of grids of at most this many points take a direct kernel (one lane per
+// word, no LDS, no barriers): a marching block walks its chunk at about a memory latency per
+// plane, 16-18 us a step however small the grid is, where the direct reads go through L2 4r + 3
+// times.  Radius 4, us a step, direct / marching: acoustic 5.4 / 16.2 at 64^3, 6.3 / 16.6 at
+// 96^3, 11.1 / 17.7 at 128^3, 19.0 / 19.0 at 160^3, 33.9 / 27.9 at 200^3 (radius 2: 15.4 / 16.8
+// and 26.8 / 26.5); VTI 26.2 / 27.7 at 150^3, 43.0 / 42.1 at 180^3.
+constexpr int64_t DIRECT_MAX = (int64_t)7 << 19;   // 3.67 M points
+
+// Grids of at most this many cells a row take flat tiles: rows of 64 lanes would leave more than
+// half of the lanes idle.  us, radius 4, rows of lanes / flat: acoustic step 47 x 400 x 300
+// 49.2 / 25.5, 64 x 400 x 300 48.2 / 29.6, 100 x 300 x 400 52.0 / 42.0, 120 x 200 x 200
+// 22.9 / 23.6; star 47 x 300 x 300 31.9 / 16.5, 100 x 300 x 300 30.2 / 20.3.  Wide grids lose:
+// the 400^3 step 209 / 226, the 512^3 star 191 / 210 (in rows of lanes a wave stays on one line
+// of memory).
+constexpr int FLAT_MAX_NX = 112;
+
+// Flat tiles, for grids too narrow for rows of 64 lanes: the lanes of a block cover a tile's rows
+// of txa <= 64 words one row after the other.  flat_tile_words is the LDS a kernel of nt lanes
+// holds per plane of a tile with its halo.
+constexpr int flat_tile_words(int r, int nt) { return (nt / 64 + 2 * r) * 66; }
+
+// Tile rows and z chunk of nt-lane blocks, `slots` of them at once; tiles of one height.
+inline void flat_tile(Geom &g, int r, int nt, int64_t slots, int zmin) {
+    g.txa = balanced_tile_words(g.nx, 64, &g.ntx);
+    int rows = nt / g.txa;
+    const int most = flat_tile_words(r, nt) / (g.txa + 2) - 2 * r;
+    if (rows > most) rows = most;
+    if (rows > 128) rows = 128;
+    g.nty = (g.ny + rows - 1) / rows;
+    g.rows = (g.ny + g.nty - 1) / g.nty;
+    g.zchunk = pick_zchunk_rounds(g.nz, (int64_t)g.ntx * g.nty, slots, zmin, 128, r);
+    g.nzc = (g.nz + g.zchunk - 1) / g.zchunk;
 }
 
 // Blocks of `kernel` (launched with `threads` threads, no dynamic LDS) that the

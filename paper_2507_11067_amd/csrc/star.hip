@@ -40,6 +40,8 @@ namespace {
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
+constexpr int SNT = 1024;   // threads of a marching block
+
 struct StarArgs {
     Geom g;
     float c[3][9];  // axis z, y, x; k + r
@@ -52,17 +54,16 @@ struct StarArgs {
 // (p - zb) mod S, S even so that the halo set index p mod 2 is fixed per phase),
 // and the loop runs in rounds of S phases with no branch inside a full round, so
 // the wait before parking a plane only covers that plane's loads.
-template <int R, int TX, int TY>
-__global__ void __launch_bounds__(TX *TY) star_kernel(StarArgs a) {
+// FLAT: the lanes cover rows of txa words one after the other (narrow grids); else a row has 64
+// lanes, of which txa own words.
+template <int R, bool FLAT>
+__global__ void __launch_bounds__(SNT) star_kernel(StarArgs a) {
     constexpr int Q = 2 * R + 1;
     constexpr int S = Q + 3;         // queue slots (even)
     constexpr int NR = R + 2;        // LDS ring planes
-    constexpr int BY = TY;
-    constexpr int LW4 = TX + 2, LH = BY + 2 * R;
-    constexpr int NT = TX * TY;
-    constexpr int NH = 2 * R * LW4 + 2 * BY;
-    constexpr int NHK = (NH + NT - 1) / NT;
-    __shared__ float4 ring[NR][LH][LW4];
+    constexpr int NT = SNT;
+    constexpr int NHK = 1;           // halo words per lane (a tile has fewer than NT)
+    __shared__ float4 ring[NR][flat_tile_words(R, NT)];
 
     const Geom &g = a.g;
     int b = mms_xcd_remap(blockIdx.x, gridDim.x);
@@ -71,13 +72,16 @@ __global__ void __launch_bounds__(TX *TY) star_kernel(StarArgs a) {
     const int tyi = b % g.nty;
     const int zci = b / g.nty;
     const int tid = threadIdx.x;
-    const int tx = tid % TX, ty = tid / TX;
-    // balanced x tiles: txa <= TX lanes of each row own words, the rest only help
-    // with the halo and the barriers
+    // txa lanes of a row own words; the others only help with the halo and the barriers.  pitch:
+    // LDS words of a tile row
     const int txa = g.txa, lw = txa + 2, bxa = 4 * txa;
-    const bool lane_on = tx < txa;
-    const int xt = txi * bxa, yt = tyi * BY;
+    const int rows = FLAT ? g.rows : 16, pitch = FLAT ? lw : 66;
+    const int ty = FLAT ? tid / txa : tid / 64, tx = FLAT ? tid - ty * txa : tid % 64;
+    const bool lane_on = FLAT ? ty < rows : tx < txa;
+    const int xt = txi * bxa, yt = tyi * rows;
     const int x0 = xt + 4 * tx, y0 = yt + ty;
+    // (idle lanes of a flat tile read its first word)
+    const int own = !FLAT || lane_on ? (R + ty) * pitch + tx + 1 : R * pitch + 1;
     const int zb = zci * g.zchunk;
     const int ze = min(zb + g.zchunk, g.nz);
     const int zmax = g.nz + R - 1;      // last plane held in memory (halo >= R)
@@ -97,8 +101,8 @@ __global__ void __launch_bounds__(TX *TY) star_kernel(StarArgs a) {
         int row, lrow, col4, x;
         if (i < 2 * R * lw) {
             const int hr = i / lw, hc = i % lw;
-            row = hr < R ? yt - R + hr : yt + BY + (hr - R);
-            lrow = hr < R ? hr : hr + BY;
+            row = hr < R ? yt - R + hr : yt + rows + (hr - R);
+            lrow = hr < R ? hr : hr + rows;
             col4 = hc;
             x = xt - 4 + 4 * hc;
         } else {
@@ -108,10 +112,10 @@ __global__ void __launch_bounds__(TX *TY) star_kernel(StarArgs a) {
             col4 = (j & 1) ? txa + 1 : 0;
             x = (j & 1) ? xt + bxa : xt - 4;
         }
-        h_on[k] = i < 2 * R * lw + 2 * BY;
+        h_on[k] = i < 2 * R * lw + 2 * rows;
         h_ok[k] = h_on[k] && (row < ylim) && (x <= nx4);
         h_off[k] = (int64_t)row * sy + x;
-        h_lds[k] = lrow * LW4 + col4;
+        h_lds[k] = lrow * pitch + col4;
     }
     auto own_load = [&](int z) { return select_load(in0 + (int64_t)z * sz + own_off, own_ok, in0); };
     auto halo_load = [&](int z, float4 *dst) {
@@ -119,9 +123,9 @@ __global__ void __launch_bounds__(TX *TY) star_kernel(StarArgs a) {
 #pragma unroll
         for (int k = 0; k < NHK; ++k) dst[k] = select_load(p + h_off[k], h_ok[k], in0);
     };
-    auto ring_store = [&](int z, const float4 &own, const float4 *halo) {
-        float4 *t = &ring[z % NR][0][0];
-        if (lane_on) t[(R + ty) * LW4 + tx + 1] = own;
+    auto ring_store = [&](int z, const float4 &word, const float4 *halo) {
+        float4 *t = &ring[z % NR][0];
+        if (lane_on) t[(R + ty) * pitch + tx + 1] = word;
 #pragma unroll
         for (int k = 0; k < NHK; ++k)
             if (h_on[k]) t[h_lds[k]] = halo[k];
@@ -152,7 +156,7 @@ __global__ void __launch_bounds__(TX *TY) star_kernel(StarArgs a) {
         const int zl = min(z + R + 2, zmax);
         q[(ph + R + 2) % S] = own_load(zl);
         halo_load(zl, hs[(ph + R + 2) % 2]);
-        const float4 *t = &ring[z % NR][0][0];
+        const float4 *t = &ring[z % NR][own];
         const float4 ctr = q[ph % S];
         float4 s;
         s.x = c[R] * ctr.x;
@@ -171,15 +175,15 @@ __global__ void __launch_bounds__(TX *TY) star_kernel(StarArgs a) {
         }
 #pragma unroll
         for (int k = -R; k <= R; ++k) {
-            const float4 v = k == 0 ? ctr : t[(R + ty + k) * LW4 + tx + 1];
+            const float4 v = k == 0 ? ctr : t[k * pitch];
             const float ck = c[9 + R + k];
             s.x = fmaf(ck, v.x, s.x);
             s.y = fmaf(ck, v.y, s.y);
             s.z = fmaf(ck, v.z, s.z);
             s.w = fmaf(ck, v.w, s.w);
         }
-        const float4 L = t[(R + ty) * LW4 + tx];
-        const float4 Rr = t[(R + ty) * LW4 + tx + 2];
+        const float4 L = t[-1];
+        const float4 Rr = t[1];
         const float w[12] = {L.x, L.y, L.z, L.w, ctr.x, ctr.y, ctr.z, ctr.w, Rr.x, Rr.y, Rr.z, Rr.w};
         float o[4] = {s.x, s.y, s.z, s.w};
 #pragma unroll
@@ -269,7 +273,6 @@ __global__ void __launch_bounds__(256) star_direct_kernel(StarArgs a, int64_t nw
 
 template <int R>
 int launch_r(const float *in, float *out, const mms_grid *gd, const float *coeffs, hipStream_t s) {
-    constexpr int TX = 64, TY = 16;
     StarArgs a{};
     Geom &g = a.g;
     g.H = gd->halo;
@@ -280,8 +283,8 @@ int launch_r(const float *in, float *out, const mms_grid *gd, const float *coeff
     g.nz = (int)gd->nz;
     g.sy = gd->sy;
     g.sz = gd->sz;
-    g.txa = balanced_tile_words(g.nx, TX, &g.ntx);
-    g.nty = (g.ny + TY - 1) / TY;
+    g.txa = balanced_tile_words(g.nx, 64, &g.ntx);
+    g.nty = (g.ny + 15) / 16;
     // one block per CU (the LDS ring fills most of a CU's LDS): enough z chunks
     // to give every CU one block, chunks of 8 to 128 planes
     const int zc = pick_zchunk(g.nz, (int64_t)g.ntx * g.nty, 256, 8, 128);
@@ -300,7 +303,14 @@ int launch_r(const float *in, float *out, const mms_grid *gd, const float *coeff
                            nxw);
         return check_launch("star_direct_kernel");
     }
-    hipLaunchKernelGGL((star_kernel<R, TX, TY>), dim3((unsigned)nblk), dim3(TX * TY), 0, s, a);
+    if (g.nx <= FLAT_MAX_NX) {
+        flat_tile(g, R, SNT, 256, 8);
+        const int64_t nflat = (int64_t)g.ntx * g.nty * g.nzc;
+        if (nflat > 0x7fffffff) return MMS_EINVAL;
+        hipLaunchKernelGGL((star_kernel<R, true>), dim3((unsigned)nflat), dim3(SNT), 0, s, a);
+    } else {
+        hipLaunchKernelGGL((star_kernel<R, false>), dim3((unsigned)nblk), dim3(SNT), 0, s, a);
+    }
     return check_launch("star_kernel");
 }
 

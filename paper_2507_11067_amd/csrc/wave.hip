@@ -30,6 +30,8 @@ enum { MODE_FWD = 0, MODE_ADJ = 1, MODE_ENERGY = 2, MODE_GRAD = 3, MODE_ADJMU = 
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
+constexpr int WNT = 1024;   // threads of a marching block
+
 struct WaveArgs {
     Geom g;
     float c[9];           // per-axis weights, k + r (symmetric)
@@ -236,16 +238,16 @@ __device__ __forceinline__ void finish_cells(const WaveArgs &a, int z, int y, in
     }
 }
 
-template <int R, int MODE, int TX, int TY>
-__global__ void __launch_bounds__(TX *TY) wave_kernel(WaveArgs a) {
+// FLAT: the lanes cover rows of txa words one after the other (narrow grids); else a row has 64
+// lanes, of which txa own words.
+template <int R, int MODE, bool FLAT>
+__global__ void __launch_bounds__(WNT) wave_kernel(WaveArgs a) {
     constexpr int Q = 2 * R + 1;
-    constexpr int BY = TY;
-    constexpr int LW4 = TX + 2, LH = BY + 2 * R;
-    constexpr int NT = TX * TY;
-    constexpr int NH = 2 * R * LW4 + 2 * BY;
-    constexpr int NHK = (NH + NT - 1) / NT;
+    constexpr int NT = WNT;
+    constexpr int TW = flat_tile_words(R, NT);
+    constexpr int NHK = 1;      // halo words per lane (a tile has fewer than NT)
     constexpr int NR = R + 2;   // LDS ring: planes z .. z+R+1
-    __shared__ float4 ring[NR][LH][LW4];
+    __shared__ float4 ring[NR][TW];
     __shared__ double sred[2 * (NT / 64)];
 
     const Geom &g = a.g;
@@ -255,13 +257,16 @@ __global__ void __launch_bounds__(TX *TY) wave_kernel(WaveArgs a) {
     const int tyi = b % g.nty;
     const int zci = b / g.nty;
     const int tid = threadIdx.x;
-    const int tx = tid % TX, ty = tid / TX;
-    // balanced x tiles: txa <= TX lanes of each row own words, the rest only help
-    // with the halo and the barriers
+    // txa lanes of a row own words; the others only help with the halo and the barriers.  pitch:
+    // LDS words of a tile row
     const int txa = g.txa, lw = txa + 2, bxa = 4 * txa;
-    const bool lane_on = tx < txa;
-    const int xt = txi * bxa, yt = tyi * BY;
+    const int rows = FLAT ? g.rows : 16, pitch = FLAT ? lw : 66;
+    const int ty = FLAT ? tid / txa : tid / 64, tx = FLAT ? tid - ty * txa : tid % 64;
+    const bool lane_on = FLAT ? ty < rows : tx < txa;
+    const int xt = txi * bxa, yt = tyi * rows;
     const int x0 = xt + 4 * tx, y = yt + ty;
+    // (idle lanes of a flat tile read its first word)
+    const int own = !FLAT || lane_on ? (R + ty) * pitch + tx + 1 : R * pitch + 1;
     const int zb = zci * g.zchunk;
     const int ze = min(zb + g.zchunk, g.nz);
     const int nx4 = (g.nx + 3) & ~3;
@@ -289,8 +294,8 @@ __global__ void __launch_bounds__(TX *TY) wave_kernel(WaveArgs a) {
         int row, lrow, col4, x;
         if (i < 2 * R * lw) {
             const int hr = i / lw, hc = i % lw;
-            row = hr < R ? yt - R + hr : yt + BY + (hr - R);
-            lrow = hr < R ? hr : hr + BY;
+            row = hr < R ? yt - R + hr : yt + rows + (hr - R);
+            lrow = hr < R ? hr : hr + rows;
             col4 = hc;
             x = xt - 4 + 4 * hc;
         } else {
@@ -300,10 +305,10 @@ __global__ void __launch_bounds__(TX *TY) wave_kernel(WaveArgs a) {
             col4 = (j & 1) ? txa + 1 : 0;
             x = (j & 1) ? xt + bxa : xt - 4;
         }
-        h_on[k] = i < 2 * R * lw + 2 * BY;
+        h_on[k] = i < 2 * R * lw + 2 * rows;
         h_ok[k] = h_on[k] && (row < ylim) && (x <= nx4);
         h_off[k] = (int64_t)row * sy + x;
-        h_lds[k] = lrow * LW4 + col4;
+        h_lds[k] = lrow * pitch + col4;
         if constexpr (MODE == MODE_ADJ) {
             const float gy = gaxis(row, g.ny, W, sa, a.faces & 4, a.faces & 8);
 #pragma unroll
@@ -341,9 +346,9 @@ __global__ void __launch_bounds__(TX *TY) wave_kernel(WaveArgs a) {
         return ld(a.f0, z, h_off[k], h_ok[k]);
     };
     // tile of one plane (own cells + halo) into ring slot `slot`
-    auto ring_store = [&](int slot, const float4 &own, const float4 *halo) {
-        float4 *t = &ring[slot][0][0];
-        if (lane_on) t[(R + ty) * LW4 + tx + 1] = own;
+    auto ring_store = [&](int slot, const float4 &field, const float4 *halo) {
+        float4 *t = &ring[slot][0];
+        if (lane_on) t[(R + ty) * pitch + tx + 1] = field;
 #pragma unroll
         for (int k = 0; k < NHK; ++k)
             if (h_on[k]) t[h_lds[k]] = halo[k];
@@ -399,12 +404,12 @@ __global__ void __launch_bounds__(TX *TY) wave_kernel(WaveArgs a) {
                 }
                 // o = S f at the lane's 4 cells
                 float o[4] = {0.f, 0.f, 0.f, 0.f};
-                const float4 *t = &ring[z % NR][0][0];
+                const float4 *t = &ring[z % NR][own];
                 const float4 ctr = q[(ph + R) % Q];
 #pragma unroll
                 for (int k = -R; k <= R; ++k) {
                     const float4 vz = q[(ph + R + k + Q) % Q];
-                    const float4 vy = k == 0 ? ctr : t[(R + ty + k) * LW4 + tx + 1];
+                    const float4 vy = k == 0 ? ctr : t[k * pitch];
                     const float ck = c[R + k];
                     o[0] = fmaf(ck, vz.x + vy.x, o[0]);
                     o[1] = fmaf(ck, vz.y + vy.y, o[1]);
@@ -412,8 +417,8 @@ __global__ void __launch_bounds__(TX *TY) wave_kernel(WaveArgs a) {
                     o[3] = fmaf(ck, vz.w + vy.w, o[3]);
                 }
                 {
-                    const float4 L = t[(R + ty) * LW4 + tx];
-                    const float4 Rr = t[(R + ty) * LW4 + tx + 2];
+                    const float4 L = t[-1];
+                    const float4 Rr = t[1];
                     const float w[12] = {L.x,   L.y,   L.z,   L.w,  ctr.x, ctr.y,
                                          ctr.z, ctr.w, Rr.x, Rr.y, Rr.z,  Rr.w};
 #pragma unroll
@@ -566,26 +571,22 @@ __global__ void record_kernel(const float *u0, float *tr, int nx, int ny, int64_
     if (x < nx) tr[(int64_t)y * nx + x] = u0[(int64_t)y * sy + x];
 }
 
-// Tile shape: up to 256 x 16 cells per block (64 x 16 lanes); the LDS ring fills most
-// of a CU's LDS, so one block runs per CU.
-constexpr int WTX = 64, WTY = 16;
-// Grids of at most this many points take the direct kernel (one lane per word, no LDS, no
-// barriers): a marching block walks its chunk at about a memory latency per plane, 16-18 us a
-// step however small the grid is, where the direct reads go through L2 4r + 3 times.  Radius 4,
-// us a step, direct / marching: 5.4 / 16.2 at 64^3, 6.3 / 16.6 at 96^3, 11.1 / 17.7 at 128^3,
-// 19.0 / 19.0 at 160^3, 33.9 / 27.9 at 200^3 (radius 2: 15.4 / 16.8 and 26.8 / 26.5).
-constexpr int64_t DIRECT_MAX = (int64_t)7 << 19;   // 3.67 M points
-
-void fill_geom(Geom &g, const mms_grid *gd) {
+void fill_sizes(Geom &g, const mms_grid *gd) {
     g.H = gd->halo;
     g.nx = (int)gd->nx;
     g.ny = (int)gd->ny;
     g.nz = (int)gd->nz;
     g.sy = gd->sy;
     g.sz = gd->sz;
-    g.txa = balanced_tile_words(g.nx, WTX, &g.ntx);
-    g.nty = (g.ny + WTY - 1) / WTY;
-    // one block per CU (LDS-bound): the columns split evenly over the CUs
+}
+
+// Tiles of up to 64 x 16 lanes; the LDS ring fills most of a CU's LDS, so one block runs per
+// CU, and the columns are split evenly over the CUs.
+void fill_geom(Geom &g, const mms_grid *gd) {
+    fill_sizes(g, gd);
+    g.txa = balanced_tile_words(g.nx, 64, &g.ntx);
+    g.rows = 16;
+    g.nty = (g.ny + 15) / 16;
     g.zchunk = pick_zchunk(g.nz, (int64_t)g.ntx * g.nty, 256, 8, 128);
     g.nzc = (g.nz + g.zchunk - 1) / g.zchunk;
 }
@@ -605,10 +606,7 @@ WaveArgs base_args(const mms_wave *w) {
 
 template <int MODE>
 int launch_mode(WaveArgs &a, const mms_grid *gd, int r, hipStream_t s) {
-    constexpr int TX = WTX, TY = WTY;
-    fill_geom(a.g, gd);
-    const int64_t nblk = (int64_t)a.g.ntx * a.g.nty * a.g.nzc;
-    if (nblk > 0x7fffffff) return MMS_EINVAL;
+    fill_sizes(a.g, gd);
     if constexpr (MODE == MODE_FWD || MODE == MODE_ADJMU || MODE == MODE_GRAD) {
         if ((int64_t)a.g.nx * a.g.ny * a.g.nz <= DIRECT_MAX) {
             const unsigned nxw = (unsigned)(a.g.nx + 3) / 4;
@@ -624,12 +622,32 @@ int launch_mode(WaveArgs &a, const mms_grid *gd, int r, hipStream_t s) {
             return check_launch("wave_direct_kernel");
         }
     }
-    const dim3 grid((unsigned)nblk), block(TX * TY);
+    // the energy's blocks stay as they are: callers size workspaces by their number
+    const bool flat = MODE != MODE_ENERGY && a.g.nx <= FLAT_MAX_NX;
+    if (flat)
+        flat_tile(a.g, r, WNT, 256, 8);
+    else
+        fill_geom(a.g, gd);
+    const int64_t nblk = (int64_t)a.g.ntx * a.g.nty * a.g.nzc;
+    if (nblk > 0x7fffffff) return MMS_EINVAL;
+    const dim3 grid((unsigned)nblk), block(WNT);
+    if constexpr (MODE != MODE_ENERGY) {
+        if (flat) {
+            switch (r) {
+                case 1: hipLaunchKernelGGL((wave_kernel<1, MODE, true>), grid, block, 0, s, a); break;
+                case 2: hipLaunchKernelGGL((wave_kernel<2, MODE, true>), grid, block, 0, s, a); break;
+                case 3: hipLaunchKernelGGL((wave_kernel<3, MODE, true>), grid, block, 0, s, a); break;
+                case 4: hipLaunchKernelGGL((wave_kernel<4, MODE, true>), grid, block, 0, s, a); break;
+                default: return MMS_EUNSUPPORTED;
+            }
+            return check_launch("wave_kernel");
+        }
+    }
     switch (r) {
-        case 1: hipLaunchKernelGGL((wave_kernel<1, MODE, TX, TY>), grid, block, 0, s, a); break;
-        case 2: hipLaunchKernelGGL((wave_kernel<2, MODE, TX, TY>), grid, block, 0, s, a); break;
-        case 3: hipLaunchKernelGGL((wave_kernel<3, MODE, TX, TY>), grid, block, 0, s, a); break;
-        case 4: hipLaunchKernelGGL((wave_kernel<4, MODE, TX, TY>), grid, block, 0, s, a); break;
+        case 1: hipLaunchKernelGGL((wave_kernel<1, MODE, false>), grid, block, 0, s, a); break;
+        case 2: hipLaunchKernelGGL((wave_kernel<2, MODE, false>), grid, block, 0, s, a); break;
+        case 3: hipLaunchKernelGGL((wave_kernel<3, MODE, false>), grid, block, 0, s, a); break;
+        case 4: hipLaunchKernelGGL((wave_kernel<4, MODE, false>), grid, block, 0, s, a); break;
         default: return MMS_EUNSUPPORTED;
     }
     return check_launch("wave_kernel");
@@ -670,7 +688,7 @@ int wave_adjoint_step(const mms_wave *w, int n, const float *l2, const float *l1
     a.out = l0 + o;
     a.resid = resid ? resid + (int64_t)n * w->g.ny * w->g.nx : nullptr;
     if (n == 0) {
-        fill_geom(a.g, &w->g);
+        fill_sizes(a.g, &w->g);
         const int64_t np = w->g.nx * w->g.ny * w->g.nz;
         const unsigned nb = (unsigned)((np + 255) / 256);
         hipLaunchKernelGGL(adjoint_first_kernel, dim3(nb), dim3(256), 0, s, a);
@@ -705,7 +723,7 @@ int wave_adjoint_mu_step(const mms_wave *w, int n, const float *m2, const float 
     a.resid = resid ? resid + (int64_t)n * w->g.ny * w->g.nx : nullptr;
     a.mu_form = 1;
     if (n == 0) {
-        fill_geom(a.g, &w->g);
+        fill_sizes(a.g, &w->g);
         const int64_t np = w->g.nx * w->g.ny * w->g.nz;
         hipLaunchKernelGGL(adjoint_first_kernel, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, s, a);
         return check_launch("adjoint_first_kernel");
@@ -730,7 +748,7 @@ int wave_adjoint_mu_step(const mms_wave *w, int n, const float *m2, const float 
 
 int wave_scale_mu(const mms_wave *w, const float *in, float *out, int dir, hipStream_t s) {
     WaveArgs a = base_args(w);
-    fill_geom(a.g, &w->g);
+    fill_sizes(a.g, &w->g);
     const int64_t o = (int64_t)w->g.halo * (w->g.sz + w->g.sy + 1);
     const int64_t np = w->g.nx * w->g.ny * w->g.nz;
     hipLaunchKernelGGL(scale_mu_kernel, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, s, a,
