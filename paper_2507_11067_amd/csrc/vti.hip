@@ -13,12 +13,17 @@
 //  * V travels through a register queue of 2r+1 planes (z terms only);
 //  * the five point-wise operands (H^{n-1}, V^{n-1}, C2, a, b) are requested one
 //    plane ahead; both outputs are written with streaming stores.
+// Small grids take a direct kernel, narrow ones flat tiles (see DIRECT_MAX, FLAT_MAX_NX).  us a
+// step, radius 4, before / with them: 64^3 13.9 / 10.8 (the host's side of a call),
+// 128^3 19.6 / 17.2, 47 x 300 x 300 67.9 / 34.6, 100 x 300 x 300 87.1 / 70.3.
 #include "mms_internal.h"
 
 namespace mms {
 namespace {
 
 typedef float f4v __attribute__((ext_vector_type(4)));
+
+constexpr int VNT = 512;
 
 struct VtiArgs {
     Geom g;
@@ -42,13 +47,77 @@ __device__ __forceinline__ void load_lds16(const float *src, float4 *dst) {
     __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
 }
 
-template <int R, int TX, int TY>
-__global__ void __launch_bounds__(TX *TY) vti_kernel(VtiArgs a) {
+// Point-wise operands of four cells: H^{n-1}, V^{n-1}, C2, a, b
+struct Pw {
+    float4 hp, vp, c2, fa, fb;
+};
+
+// New values of both fields at the cells (z, y, x0 ..) from S_xy H, S_zz V and the operands.
+__device__ __forceinline__ void update_cells(const VtiArgs &a, int z, int y, int x0, float gz,
+                                             const float *gown, const float4 &hc4,
+                                             const float4 &vc4, const float *sxy, const float *szz,
+                                             const Pw &pw, float srcv, float *rh, float *rv) {
+    const float hcv[4] = {hc4.x, hc4.y, hc4.z, hc4.w};
+    const float vcv[4] = {vc4.x, vc4.y, vc4.z, vc4.w};
+    const float hpv[4] = {pw.hp.x, pw.hp.y, pw.hp.z, pw.hp.w};
+    const float vpv[4] = {pw.vp.x, pw.vp.y, pw.vp.z, pw.vp.w};
+    const float c2v[4] = {pw.c2.x, pw.c2.y, pw.c2.z, pw.c2.w};
+    const float fav[4] = {pw.fa.x, pw.fa.y, pw.fa.z, pw.fa.w};
+    const float fbv[4] = {pw.fb.x, pw.fb.y, pw.fb.z, pw.fb.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float G = gz * gown[e];
+        const float C2 = a.c2s * c2v[e];
+        rh[e] = G * (2.0f * hcv[e] - G * hpv[e] + C2 * (fav[e] * sxy[e] + fbv[e] * szz[e]));
+        rv[e] = G * (2.0f * vcv[e] - G * vpv[e] + C2 * (fbv[e] * sxy[e] + szz[e]));
+    }
+    if (srcv != 0.f && z == a.src_z && y == a.src_y && a.src_x >= x0 &&
+        a.src_x < x0 + 4) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (x0 + e == a.src_x) {
+                rh[e] += srcv;
+                rv[e] += srcv;
+            }
+    }
+}
+
+// Streaming stores of both fields at four cells (plane offset off) and the receivers' reading.
+__device__ __forceinline__ void store_cells(const VtiArgs &a, int z, int y, int x0, int64_t off,
+                                            const float4 &hc4, const float *rh, const float *rv) {
+    const Geom &g = a.g;
+    const int64_t sz = g.sz;
+    const float hcv[4] = {hc4.x, hc4.y, hc4.z, hc4.w};
+    float *ph_ = a.hn + (int64_t)z * sz + off;
+    float *pv_ = a.vn + (int64_t)z * sz + off;
+    if (x0 + 3 < g.nx) {
+        const f4v vh = {rh[0], rh[1], rh[2], rh[3]};
+        const f4v vv = {rv[0], rv[1], rv[2], rv[3]};
+        __builtin_nontemporal_store(vh, reinterpret_cast<f4v *>(ph_));
+        __builtin_nontemporal_store(vv, reinterpret_cast<f4v *>(pv_));
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (x0 + e < g.nx) {
+                ph_[e] = rh[e];
+                pv_[e] = rv[e];
+            }
+    }
+    if (a.traces && z == 0) {
+        float *pt = a.traces + (int64_t)y * g.nx + x0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (x0 + e < g.nx) pt[e] = hcv[e];
+    }
+}
+
+// FLAT: the lanes cover rows of txa words one after the other; else a row has 64 lanes, of which
+// txa own words.
+template <int R, bool FLAT>
+__global__ void __launch_bounds__(VNT) vti_kernel(VtiArgs a) {
     constexpr int Q = 2 * R + 1;
-    constexpr int BY = TY;
-    constexpr int LW4 = TX + 2, LH = BY + 2 * R;
-    constexpr int NT = TX * TY;
-    constexpr int NL = LH * LW4;              // words of the H tile, row-major
+    constexpr int NT = VNT;
+    constexpr int NL = flat_tile_words(R, NT);   // words of the largest H tile, row-major
     constexpr int NLK = (NL + NT - 1) / NT;
     // two arrays, each step's buffer fixed at compile time (phases in pairs), so that the
     // compiler does not wait on the direct loads before the current plane's reads
@@ -62,13 +131,17 @@ __global__ void __launch_bounds__(TX *TY) vti_kernel(VtiArgs a) {
     const int tyi = b % g.nty;
     const int zci = b / g.nty;
     const int tid = threadIdx.x;
-    const int tx = tid % TX, ty = tid / TX;
-    // balanced x tiles: txa <= TX lanes of each row own words, the rest only help
-    // with the halo and the barriers
+    // txa lanes of a row own words; the others only help with the halo and the barriers.  pitch:
+    // LDS words of a tile row
     const int txa = g.txa, lw = txa + 2, bxa = 4 * txa;
-    const bool lane_on = tx < txa;
-    const int xt = txi * bxa, yt = tyi * BY;
+    const int rows = FLAT ? g.rows : NT / 64, pitch = FLAT ? lw : 66;
+    const int ty = FLAT ? tid / txa : tid / 64, tx = FLAT ? tid - ty * txa : tid % 64;
+    const bool lane_on = FLAT ? ty < rows : tx < txa;
+    const int nw = FLAT ? (rows + 2 * R) * lw : NL;
+    const int xt = txi * bxa, yt = tyi * rows;
     const int x0 = xt + 4 * tx, y = yt + ty;
+    // (idle lanes of a flat tile read its first word)
+    const int own = !FLAT || lane_on ? (R + ty) * pitch + tx + 1 : R * pitch + 1;
     const int zb = zci * g.zchunk;
     const int ze = min(zb + g.zchunk, g.nz);
     const int nx4 = (g.nx + 3) & ~3;
@@ -88,15 +161,15 @@ __global__ void __launch_bounds__(TX *TY) vti_kernel(VtiArgs a) {
     auto ld = [&](const float *base, int z, int64_t off, bool ok) -> float4 {
         return guarded_load(base + (int64_t)z * sz + off, ok, a.c2);
     };
-    // H tile word i -> (row i / LW4, col i % LW4) from the tile origin (row yt - R, column
+    // H tile word i -> (row i / pitch, col i % pitch) from the tile origin (row yt - R, column
     // xt - 4); words outside this tile's lw columns or outside the array are read from the
     // origin instead (never used)
     uint32_t d_off[NLK];
 #pragma unroll
     for (int k = 0; k < NLK; ++k) {
         const int i = tid + k * NT;
-        const int row = i / LW4, col = i % LW4;
-        const bool ok = (i < NL) && (col < lw) && (yt - R + row < ylim) && (xt - 4 + 4 * col <= nx4);
+        const int row = i / pitch, col = i % pitch;
+        const bool ok = (i < nw) && (col < lw) && (yt - R + row < ylim) && (xt - 4 + 4 * col <= nx4);
         d_off[k] = ok ? (uint32_t)row * (uint32_t)sy + 4u * (uint32_t)col : 0u;
     }
     const int wave_base = __builtin_amdgcn_readfirstlane(tid & ~63);
@@ -104,13 +177,9 @@ __global__ void __launch_bounds__(TX *TY) vti_kernel(VtiArgs a) {
         const float *p = a.hc + (int64_t)z * sz + (int64_t)(yt - R) * sy + (xt - 4);
 #pragma unroll
         for (int k = 0; k < NLK; ++k)
-            if (tid + k * NT < NL) load_lds16(p + d_off[k], t + wave_base + k * NT);
+            if (tid + k * NT < nw) load_lds16(p + d_off[k], t + wave_base + k * NT);
     };
 
-    // point-wise operands of a plane: H^{n-1}, V^{n-1}, C2, a, b
-    struct Pw {
-        float4 hp, vp, c2, fa, fb;
-    };
     auto load_pw = [&](int z) {
         Pw p;
         p.hp = ld(a.hp, z, own_off, own_ok);
@@ -148,17 +217,17 @@ __global__ void __launch_bounds__(TX *TY) vti_kernel(VtiArgs a) {
                     load_tile(z + 1, nxt);
                     npw = load_pw(z + 1);
                 }
-                const float4 *t = cur;
-                const float4 hc4 = t[(R + ty) * LW4 + tx + 1];
-                const float4 L = t[(R + ty) * LW4 + tx];
-                const float4 Rr = t[(R + ty) * LW4 + tx + 2];
+                const float4 *t = cur + own;
+                const float4 hc4 = t[0];
+                const float4 L = t[-1];
+                const float4 Rr = t[1];
                 const float w[12] = {L.x,   L.y,   L.z,   L.w,  hc4.x, hc4.y,
                                      hc4.z, hc4.w, Rr.x, Rr.y, Rr.z,  Rr.w};
                 float sxy[4] = {0.f, 0.f, 0.f, 0.f}, szz[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int k = -R; k <= R; ++k) {
                     const float ck = c[R + k];
-                    const float4 vy = k == 0 ? hc4 : t[(R + ty + k) * LW4 + tx + 1];
+                    const float4 vy = k == 0 ? hc4 : t[k * pitch];
                     const float4 vz = q[(ph % Q + R + k + Q) % Q];
                     const float yv[4] = {vy.x, vy.y, vy.z, vy.w};
                     const float zv[4] = {vz.x, vz.y, vz.z, vz.w};
@@ -170,58 +239,14 @@ __global__ void __launch_bounds__(TX *TY) vti_kernel(VtiArgs a) {
                 }
                 const float gz = gaxis(z, g.nz, W, sa, zlo, zhi);
                 const float4 vc4 = q[(ph % Q + R) % Q];
-                const float hcv[4] = {hc4.x, hc4.y, hc4.z, hc4.w};
-                const float vcv[4] = {vc4.x, vc4.y, vc4.z, vc4.w};
-                const float hpv[4] = {pw.hp.x, pw.hp.y, pw.hp.z, pw.hp.w};
-                const float vpv[4] = {pw.vp.x, pw.vp.y, pw.vp.z, pw.vp.w};
-                const float c2v[4] = {pw.c2.x, pw.c2.y, pw.c2.z, pw.c2.w};
-                const float fav[4] = {pw.fa.x, pw.fa.y, pw.fa.z, pw.fa.w};
-                const float fbv[4] = {pw.fb.x, pw.fb.y, pw.fb.z, pw.fb.w};
                 float rh[4], rv[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float G = gz * gown[e];
-                    const float C2 = a.c2s * c2v[e];
-                    rh[e] = G * (2.0f * hcv[e] - G * hpv[e] + C2 * (fav[e] * sxy[e] + fbv[e] * szz[e]));
-                    rv[e] = G * (2.0f * vcv[e] - G * vpv[e] + C2 * (fbv[e] * sxy[e] + szz[e]));
-                }
-                if (srcv != 0.f && z == a.src_z && y == a.src_y && a.src_x >= x0 &&
-                    a.src_x < x0 + 4) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (x0 + e == a.src_x) {
-                            rh[e] += srcv;
-                            rv[e] += srcv;
-                        }
-                }
+                update_cells(a, z, y, x0, gz, gown, hc4, vc4, sxy, szz, pw, srcv, rh, rv);
                 // the next H tile is in LDS once this lane's requests are done; the barrier
                 // publishes every lane's words and ends all reads of this plane; the output
                 // stores come after it, so that the wait does not cover them
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 __syncthreads();
-                if (lane_on && y < g.ny && x0 < g.nx) {
-                    float *ph_ = a.hn + (int64_t)z * sz + own_off;
-                    float *pv_ = a.vn + (int64_t)z * sz + own_off;
-                    if (x0 + 3 < g.nx) {
-                        const f4v vh = {rh[0], rh[1], rh[2], rh[3]};
-                        const f4v vv = {rv[0], rv[1], rv[2], rv[3]};
-                        __builtin_nontemporal_store(vh, reinterpret_cast<f4v *>(ph_));
-                        __builtin_nontemporal_store(vv, reinterpret_cast<f4v *>(pv_));
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (x0 + e < g.nx) {
-                                ph_[e] = rh[e];
-                                pv_[e] = rv[e];
-                            }
-                    }
-                    if (a.traces && z == 0) {
-                        float *pt = a.traces + (int64_t)y * g.nx + x0;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (x0 + e < g.nx) pt[e] = hcv[e];
-                    }
-                }
+                if (lane_on && y < g.ny && x0 < g.nx) store_cells(a, z, y, x0, own_off, hc4, rh, rv);
                 if (more) {
                     q[ph % Q] = nq;
                     pw = npw;
@@ -232,7 +257,57 @@ __global__ void __launch_bounds__(TX *TY) vti_kernel(VtiArgs a) {
     }
 }
 
-constexpr int VTX = 64, VTY = 8;
+// Small grids: one lane per 16-byte word reads its words of H (row and column) and V (z) straight
+// from memory (the operations, and their order, are those of vti_kernel).
+template <int R>
+__global__ void __launch_bounds__(256) vti_direct_kernel(VtiArgs a, unsigned nwords, unsigned nxw) {
+    const unsigned i = (unsigned)mms_xcd_remap(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
+    if (i >= nwords) return;
+    const Geom &g = a.g;
+    const unsigned row = i / nxw;
+    const int x0 = 4 * (int)(i % nxw), y = (int)(row % (unsigned)g.ny), z = (int)(row / (unsigned)g.ny);
+    const int64_t off = (int64_t)y * g.sy + x0, zoff = (int64_t)z * g.sz + off;
+    auto ld = [](const float *q) { return *reinterpret_cast<const float4 *>(q); };
+    const float *h = a.hc + zoff, *v = a.vc + zoff;
+    const float4 L = ld(h - 4), hc4 = ld(h), Rr = ld(h + 4), vc4 = ld(v);
+    float4 vy[2 * R + 1], vz[2 * R + 1];
+#pragma unroll
+    for (int k = -R; k <= R; ++k) {
+        vy[k + R] = k == 0 ? hc4 : ld(h + k * g.sy);
+        vz[k + R] = k == 0 ? vc4 : ld(v + k * g.sz);
+    }
+    Pw pw;
+    pw.hp = ld(a.hp + zoff);
+    pw.vp = ld(a.vp + zoff);
+    pw.c2 = ld(a.c2 + zoff);
+    pw.fa = ld(a.fa + zoff);
+    pw.fb = ld(a.fb + zoff);
+    const float srcv = a.src ? *a.src : 0.f;
+    const int W = a.sponge_w;
+    const float sa = a.sponge_a;
+    float gown[4];
+    const float gy = gaxis(y, g.ny, W, sa, a.faces & 4, a.faces & 8);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) gown[e] = gy * gaxis(x0 + e, g.nx, W, sa, a.faces & 1, a.faces & 2);
+    const float gz = gaxis(z, g.nz, W, sa, a.faces & 16, a.faces & 32);
+    const float w[12] = {L.x,   L.y,   L.z,   L.w,  hc4.x, hc4.y,
+                         hc4.z, hc4.w, Rr.x, Rr.y, Rr.z,  Rr.w};
+    float sxy[4] = {0.f, 0.f, 0.f, 0.f}, szz[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = -R; k <= R; ++k) {
+        const float ck = a.c[R + k];
+        const float yv[4] = {vy[R + k].x, vy[R + k].y, vy[R + k].z, vy[R + k].w};
+        const float zv[4] = {vz[R + k].x, vz[R + k].y, vz[R + k].z, vz[R + k].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            sxy[e] = fmaf(ck, yv[e] + w[4 + e + k], sxy[e]);
+            szz[e] = fmaf(ck, zv[e], szz[e]);
+        }
+    }
+    float rh[4], rv[4];
+    update_cells(a, z, y, x0, gz, gown, hc4, vc4, sxy, szz, pw, srcv, rh, rv);
+    store_cells(a, z, y, x0, off, hc4, rh, rv);
+}
 
 }  // namespace
 
@@ -249,16 +324,18 @@ int vti_step(const mms_wave *w, int n, const float *fa, const float *fb, const f
     g.sy = gd->sy;
     g.sz = gd->sz;
     // the H tile is addressed with 32-bit offsets from its origin
-    if ((int64_t)(VTY + 2 * w->radius + 1) * g.sy >= ((int64_t)1 << 32)) {
+    if ((int64_t)(8 + 2 * w->radius + 1) * g.sy >= ((int64_t)1 << 32)) {
         set_last_error("VTI step: grid rows too long for 32-bit tile offsets");
         return MMS_EUNSUPPORTED;
     }
-    g.txa = balanced_tile_words(g.nx, VTX, &g.ntx);
-    g.nty = (g.ny + VTY - 1) / VTY;
+    const bool flat = g.nx <= FLAT_MAX_NX;
+    g.txa = balanced_tile_words(g.nx, 64, &g.ntx);
+    g.nty = (g.ny + 7) / 8;
     // one 512-thread block per CU (VGPR-bound), 256 CUs; the V queue fill costs
     // about one plane of traffic
     g.zchunk = pick_zchunk_rounds(g.nz, (int64_t)g.ntx * g.nty, 256, 8, 128, 1);
     g.nzc = (g.nz + g.zchunk - 1) / g.zchunk;
+    if (flat) flat_tile(g, w->radius, VNT, 256, 8);
     const int r = w->radius;
     for (int k = -r; k <= r; ++k) a.c[k + r] = w->lap[k < 0 ? -k : k];
     const int64_t o = (int64_t)gd->halo * (gd->sz + gd->sy + 1);
@@ -280,14 +357,31 @@ int vti_step(const mms_wave *w, int n, const float *fa, const float *fb, const f
     a.sponge_w = w->sponge_width;
     a.sponge_a = w->sponge_alpha;
     a.faces = w->sponge_faces;
+    if ((int64_t)g.nx * g.ny * g.nz <= DIRECT_MAX) {
+        const unsigned nxw = (unsigned)(g.nx + 3) / 4;
+        const unsigned nwords = nxw * (unsigned)g.ny * (unsigned)g.nz;
+        const dim3 grid((nwords + 255) / 256), block(256);
+        switch (r) {
+            case 1: hipLaunchKernelGGL((vti_direct_kernel<1>), grid, block, 0, s, a, nwords, nxw); break;
+            case 2: hipLaunchKernelGGL((vti_direct_kernel<2>), grid, block, 0, s, a, nwords, nxw); break;
+            case 3: hipLaunchKernelGGL((vti_direct_kernel<3>), grid, block, 0, s, a, nwords, nxw); break;
+            case 4: hipLaunchKernelGGL((vti_direct_kernel<4>), grid, block, 0, s, a, nwords, nxw); break;
+            default: return MMS_EUNSUPPORTED;
+        }
+        return check_launch("vti_direct_kernel");
+    }
     const int64_t nblk = (int64_t)g.ntx * g.nty * g.nzc;
     if (nblk > 0x7fffffff) return MMS_EINVAL;
-    const dim3 grid((unsigned)nblk), block(VTX * VTY);
-    switch (r) {
-        case 1: hipLaunchKernelGGL((vti_kernel<1, VTX, VTY>), grid, block, 0, s, a); break;
-        case 2: hipLaunchKernelGGL((vti_kernel<2, VTX, VTY>), grid, block, 0, s, a); break;
-        case 3: hipLaunchKernelGGL((vti_kernel<3, VTX, VTY>), grid, block, 0, s, a); break;
-        case 4: hipLaunchKernelGGL((vti_kernel<4, VTX, VTY>), grid, block, 0, s, a); break;
+    const dim3 grid((unsigned)nblk), block(VNT);
+    switch (2 * r + flat) {
+        case 2: hipLaunchKernelGGL((vti_kernel<1, false>), grid, block, 0, s, a); break;
+        case 3: hipLaunchKernelGGL((vti_kernel<1, true>), grid, block, 0, s, a); break;
+        case 4: hipLaunchKernelGGL((vti_kernel<2, false>), grid, block, 0, s, a); break;
+        case 5: hipLaunchKernelGGL((vti_kernel<2, true>), grid, block, 0, s, a); break;
+        case 6: hipLaunchKernelGGL((vti_kernel<3, false>), grid, block, 0, s, a); break;
+        case 7: hipLaunchKernelGGL((vti_kernel<3, true>), grid, block, 0, s, a); break;
+        case 8: hipLaunchKernelGGL((vti_kernel<4, false>), grid, block, 0, s, a); break;
+        case 9: hipLaunchKernelGGL((vti_kernel<4, true>), grid, block, 0, s, a); break;
         default: return MMS_EUNSUPPORTED;
     }
     return check_launch("vti_kernel");
