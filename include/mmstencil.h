@@ -161,6 +161,16 @@ int mms_wave_forward(const mms_wave *w, int n_begin, int n_end, float *const *st
                      void *stream);
 
 /*
+ * mms_wave_forward_keep -- mms_wave_forward that also writes the stencil values S(u^n) of step
+ * n = n_begin + i to the grid kept[i] (interior only; a HOST array of device pointers with
+ * entries that may be NULL, or NULL).  They are what a gradient needs of u^n, so a backward pass
+ * that has them runs no stencil over the forward levels (mms_wave_adjoint_mu_keep).  A kept grid
+ * must not overlap the levels of its step or c2, and the problem must have no image.
+ */
+int mms_wave_forward_keep(const mms_wave *w, int n_begin, int n_end, float *const *states,
+                          float *const *kept, void *stream);
+
+/*
  * mms_wave_adjoint_step -- one step n of the exact discrete adjoint of the
  * recurrence above (the transpose of the state map (u^n, u^{n-1}) ->
  * (u^{n+1}, u^n); the paper has no adjoint).  For n >= 1:
@@ -266,6 +276,17 @@ int mms_tti_step(const mms_wave *w, const mms_tti *t, int n, const float *p_prev
  */
 int mms_wave_adjoint_mu(const mms_wave *w, int n_hi, int n_lo, float *const *mus,
                         const float *const *us, const float *resid, double *grad, void *stream);
+
+/*
+ * mms_wave_adjoint_mu_keep -- mms_wave_adjoint_mu that takes the gradient's stencil values from
+ * kept[i] = S(u^{n_lo+i}) (mms_wave_forward_keep) where that is not NULL, and from us[i] where it
+ * is; us[i] is not read where kept[i] is given.  The gradient is the same bit for bit: terms are
+ * added in the same order, up to three of one block in one step.  No kept grid may overlap a
+ * level mus that the call writes.
+ */
+int mms_wave_adjoint_mu_keep(const mms_wave *w, int n_hi, int n_lo, float *const *mus,
+                             const float *const *us, const float *const *kept, const float *resid,
+                             double *grad, void *stream);
 
 /*
  * mms_wave_scale_mu -- out = C2 G in (dir = +1: lam -> mu) or out = in / (C2 G)

@@ -206,6 +206,17 @@ class Wave:
         check(lib().mms_wave_forward(ctypes.byref(self._w), int(n_begin), int(n_end), arr,
                                      _stream(stream)), "mms_wave_forward")
 
+    def forward_keep(self, n_begin, n_end, states, kept, stream=None):
+        """forward, with the stencil values S(u^n) of step n_begin + i written to kept[i] (a grid,
+        or None); see mms_wave_forward_keep."""
+        g = self.grid
+        if len(states) < n_end - n_begin + 2 or len(kept) < n_end - n_begin:
+            raise ValueError("states or kept too short")
+        sa = (ctypes.c_void_p * len(states))(*[_grid_ptr(s, g, "state") for s in states])
+        ka = (ctypes.c_void_p * max(len(kept), 1))(*[_grid_ptr(s, g, "kept") for s in kept])
+        check(lib().mms_wave_forward_keep(ctypes.byref(self._w), int(n_begin), int(n_end), sa, ka,
+                                          _stream(stream)), "mms_wave_forward_keep")
+
     def adjoint_step(self, n, lam_np2, lam_np1, lam_n, resid=None, u_n=None, grad=None,
                      stream=None):
         g = self.grid
@@ -248,6 +259,21 @@ class Wave:
             ctypes.byref(self._w), int(n_hi), int(n_lo), ma, ua,
             _dev_ptr(resid, "resid", torch.float32, self.nt * g.ny * g.nx),
             _dev_ptr(grad, "grad", torch.float64, g.points), _stream(stream)), "mms_wave_adjoint_mu")
+
+    def adjoint_mu_keep(self, n_hi, n_lo, mus, us, kept, resid=None, grad=None, stream=None):
+        """adjoint_mu with the stencil values kept[i] = S(u^{n_lo+i}) of a forward_keep call where
+        it is not None (us[i] may be None there); see mms_wave_adjoint_mu_keep."""
+        g = self.grid
+        n = n_hi - n_lo + 1
+        if len(mus) < n + 2 or len(us) < n or len(kept) < n:
+            raise ValueError("mus, us or kept too short")
+        ptrs = [(ctypes.c_void_p * len(v))(*[_grid_ptr(t, g, name) for t in v])
+                for v, name in ((mus, "mu"), (us, "u"), (kept, "kept"))]
+        check(lib().mms_wave_adjoint_mu_keep(
+            ctypes.byref(self._w), int(n_hi), int(n_lo), *ptrs,
+            _dev_ptr(resid, "resid", torch.float32, self.nt * g.ny * g.nx),
+            _dev_ptr(grad, "grad", torch.float64, g.points), _stream(stream)),
+            "mms_wave_adjoint_mu_keep")
 
     def scale_mu(self, inp, out, direction, stream=None):
         """out = C2 G inp (direction +1, lam -> mu) or inp / (C2 G) (direction -1)."""

@@ -17,7 +17,7 @@ EXPORTS = ("mms_stencil_apply", "mms_wave_step", "mms_wave_record", "mms_wave_fo
            "mms_flat_dot_f64", "mms_flat_misfit_f64", "mms_dense_to_grid", "mms_grid_aligned",
            "mms_strerror", "mms_last_error", "mms_abi_version", "mms_vti_step", "mms_tti_step",
            "mms_wave_energy_work", "mms_flat_scale_f32", "mms_check_reduction",
-           "mms_wave_energy_noalloc")
+           "mms_wave_energy_noalloc", "mms_wave_forward_keep", "mms_wave_adjoint_mu_keep")
 
 
 class MmsGrid(ctypes.Structure):
@@ -72,6 +72,9 @@ def lib():
                                        vp, vp]
         L.mms_wave_adjoint_mu.argtypes = [wp, i32, i32, ctypes.POINTER(vp), ctypes.POINTER(vp),
                                           vp, vp, vp]
+        L.mms_wave_forward_keep.argtypes = [wp, i32, i32, ctypes.POINTER(vp), ctypes.POINTER(vp), vp]
+        L.mms_wave_adjoint_mu_keep.argtypes = [wp, i32, i32, ctypes.POINTER(vp),
+                                               ctypes.POINTER(vp), ctypes.POINTER(vp), vp, vp, vp]
         L.mms_wave_scale_mu.argtypes = [wp, vp, vp, i32, vp]
         L.mms_grid_aligned.argtypes = [i64, i64, i64, ctypes.c_int32, gp, ctypes.POINTER(i64)]
         L.mms_wave_energy_work.argtypes = [wp, ctypes.POINTER(i64)]

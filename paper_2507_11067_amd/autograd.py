@@ -13,10 +13,10 @@ WavePropagate.apply(m, u0, u1, problem) -> traces [nt, ny, nx]
 
 Memory plan: the forward pass keeps the pair (u^k, u^{k+1}) at every level
 k = 0, K, 2K, ... .  The backward pass walks the segments [k, k+K) from the
-last to the first: it recomputes u^{k+2} .. u^{k+K-1} from the pair into K - 2
-buffers, then runs the adjoint steps k+K-1 .. k, which read u^n from the pair
-and those buffers and accumulate the FP64 gradient.  Extra cost: one more forward
-sweep; extra memory: 2 nt/K + K grids.  With Problem.store_all the forward
+last to the first: it recomputes u^{k+2} .. u^{k+K-1} from the pair, keeping the
+stencil values S(u^n) in K - 2 buffers (in the lam form the levels themselves),
+then runs the adjoint steps k+K-1 .. k, which accumulate the FP64 gradient from
+them.  Extra cost: one more forward sweep; extra memory: 2 nt/K + K grids.  With Problem.store_all the forward
 pass writes every level into a grid of its own instead (nt + 1 grids, 74 GB
 for 256^3 x 1000 steps, within one MI355X's 288 GB) and the backward pass
 runs the adjoint over all steps in one call with no recompute.
@@ -123,8 +123,15 @@ class WavePropagate(torch.autograd.Function):
         # cell by cell (256^3: 45 us a step in place, 50 with three buffers, whose fourth field
         # no longer fits the 256 MB cache beside C2)
         lam = [g.zeros(dev) for _ in range(2)]
-        # levels k+2 .. of a segment; its first two are the checkpoint itself
-        seg = [] if ctx.levels is not None else [g.zeros(dev) for _ in range(min(K, max(nt, 1)) - 2)]
+        # a segment's levels u^k .. u^hi: the first two are the checkpoint itself.  The mu form
+        # keeps S(u^n) of the others, all that the gradient needs of them, while the levels go
+        # round two buffers; the lam form keeps the levels
+        inner = 0 if ctx.levels is not None else max(min(K, max(nt, 1)) - 2, 0)
+        if mu_form:
+            turn = [g.zeros(dev) for _ in range(min(inner, 2))]
+            keep = [torch.empty(g.shape, dtype=torch.float32, device=dev) for _ in range(inner)]
+        else:
+            seg = [g.zeros(dev) for _ in range(inner)]
         grad = torch.zeros((g.nz, g.ny, g.nx), dtype=torch.float64, device=dev)
         if prob.grad_block > 1:
             # each block of grad_block adjoint steps is summed in FP32, then added in FP64
@@ -138,12 +145,22 @@ class WavePropagate(torch.autograd.Function):
         for si in range(len(ctx.ckpts) - 1, -1, -1):
             k = si * K
             hi = min(k + K, nt) - 1
-            us = (list(ctx.ckpts[si]) + seg)[0:hi - k + 1]   # u^k .. u^hi
-            if hi >= k + 2:
-                w_src.forward(k + 1, hi, us)
-                recomputed += hi - k - 1
-            adjoint(hi, k, [lam[(k + i) % 2] for i in range(hi - k + 3)],
-                    us=us, resid=resid, grad=grad)
+            lams = [lam[(k + i) % 2] for i in range(hi - k + 3)]
+            n = max(hi - k - 1, 0)         # steps k+1 .. hi-1 are run again
+            recomputed += n
+            if mu_form:
+                us = (list(ctx.ckpts[si]) + [turn[i % 2] for i in range(n)])[0:hi - k + 1]
+                if n:
+                    w_src.forward_keep(k + 1, hi, us, keep[:n])
+                # u^k and u^hi are still there; S of the levels between them is kept
+                inside = [None] * n
+                wa.adjoint_mu_keep(hi, k, lams, us[:1] + inside + us[n + 1:],
+                                   [None] + keep[:n] + [None] * (hi > k), resid, grad)
+            else:
+                us = (list(ctx.ckpts[si]) + seg)[0:hi - k + 1]   # u^k .. u^hi
+                if n:
+                    w_src.forward(k + 1, hi, us)
+                adjoint(hi, k, lams, us=us, resid=resid, grad=grad)
         if mu_form:
             for b in lam:
                 wa.scale_mu(b, b, -1)      # mu^0, mu^1 -> lam^0, lam^1

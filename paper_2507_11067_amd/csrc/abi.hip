@@ -12,12 +12,13 @@
 namespace mms {
 
 int wave_step(const mms_wave *w, int n, const float *up, const float *uc, float *un, int lag,
-              hipStream_t s);
+              float *sout, hipStream_t s);
 int wave_adjoint_step(const mms_wave *w, int n, const float *l2, const float *l1, float *l0,
                       const float *resid, const float *un, double *grad, hipStream_t s);
 int wave_record(const mms_wave *w, int n, const float *u, hipStream_t s);
 int wave_adjoint_mu_step(const mms_wave *w, int n, const float *m2, const float *m1, float *m0,
-                         const float *resid, const float *un, double *grad, hipStream_t s);
+                         const float *resid, const float *un, const float *const *kept, int first,
+                         int last, double *grad, hipStream_t s);
 int wave_scale_mu(const mms_wave *w, const float *in, float *out, int dir, hipStream_t s);
 int wave_energy(const mms_wave *w, const float *un, const float *unp1, double *out, double *partials,
                 hipStream_t s);
@@ -195,7 +196,7 @@ int mms_wave_step(const mms_wave *w, int n, const float *u_prev, const float *u_
     if (overlap(u_cur, bytes, u_next, bytes)) return MMS_EINVAL;
     if (u_prev != u_next && overlap(u_prev, bytes, u_next, bytes)) return MMS_EINVAL;
     if (grid_empty(&w->g)) return MMS_OK;
-    return wave_step(w, n, u_prev, u_cur, u_next, 0, (hipStream_t)stream);
+    return wave_step(w, n, u_prev, u_cur, u_next, 0, nullptr, (hipStream_t)stream);
 }
 
 int mms_vti_step(const mms_wave *w, int n, const float *a, const float *b, const float *h_prev,
@@ -261,9 +262,11 @@ int mms_wave_record(const mms_wave *w, int n, const float *u, void *stream) {
     return wave_record(w, n, u, (hipStream_t)stream);
 }
 
-int mms_wave_forward(const mms_wave *w, int n_begin, int n_end, float *const *states, void *stream) {
+int mms_wave_forward_keep(const mms_wave *w, int n_begin, int n_end, float *const *states,
+                          float *const *kept, void *stream) {
     if (int rc = wave_ok(w)) return rc;
     if (!states || n_begin < 1 || n_end > w->nt || n_end < n_begin) return MMS_EINVAL;
+    if (kept && w->image) return MMS_EINVAL;
     const int64_t bytes = grid_elems(&w->g) * (int64_t)sizeof(float);
     for (int n = n_begin; n < n_end; ++n) {
         const int i = n - n_begin;  // states[i] = u^{n-1}, states[i+1] = u^n, states[i+2] = u^{n+1}
@@ -272,6 +275,11 @@ int mms_wave_forward(const mms_wave *w, int n_begin, int n_end, float *const *st
         if (!aligned16(up) || !aligned16(uc) || !aligned16(un)) return MMS_EINVAL;
         if (overlap(uc, bytes, un, bytes)) return MMS_EINVAL;
         if (up != un && overlap(up, bytes, un, bytes)) return MMS_EINVAL;
+        if (float *k = kept ? kept[i] : nullptr) {
+            if (!aligned16(k) || overlap(k, bytes, up, bytes) || overlap(k, bytes, uc, bytes) ||
+                overlap(k, bytes, un, bytes) || overlap(k, bytes, w->c2, bytes))
+                return MMS_EINVAL;
+        }
     }
     if (grid_empty(&w->g)) return MMS_OK;
     // Step n holds u^{n-1}, u^n and u^{n+1} in registers, so the image terms of three steps of
@@ -291,10 +299,14 @@ int mms_wave_forward(const mms_wave *w, int n_begin, int n_end, float *const *st
             ++pending;
         }
         if (int rc = wave_step(w, n, states[i], states[i + 1], states[i + 2], lag,
-                               (hipStream_t)stream))
+                               kept ? kept[i] : nullptr, (hipStream_t)stream))
             return rc;
     }
     return MMS_OK;
+}
+
+int mms_wave_forward(const mms_wave *w, int n_begin, int n_end, float *const *states, void *stream) {
+    return mms_wave_forward_keep(w, n_begin, n_end, states, nullptr, stream);
 }
 
 int mms_wave_adjoint_step(const mms_wave *w, int n, const float *lam_np2, const float *lam_np1,
@@ -328,35 +340,71 @@ int mms_wave_adjoint(const mms_wave *w, int n_hi, int n_lo, float *const *lams,
     return MMS_OK;
 }
 
-int mms_wave_adjoint_mu(const mms_wave *w, int n_hi, int n_lo, float *const *mus,
-                        const float *const *us, const float *resid, double *grad, void *stream) {
+int mms_wave_adjoint_mu_keep(const mms_wave *w, int n_hi, int n_lo, float *const *mus,
+                             const float *const *us, const float *const *kept, const float *resid,
+                             double *grad, void *stream) {
     if (int rc = wave_ok(w)) return rc;
     if (!mus || n_lo < 0 || n_hi >= w->nt || n_hi < n_lo) return MMS_EINVAL;
-    if (grad && !us) return MMS_EINVAL;
+    if (grad && !us && !kept) return MMS_EINVAL;
     if (grad && w->acc_block > 1 && !w->acc_part) return MMS_EINVAL;
     const int64_t bytes = grid_elems(&w->g) * (int64_t)sizeof(float);
+    auto keeps = [&](int n) -> const float * { return kept && n >= n_lo ? kept[n - n_lo] : nullptr; };
     // every step's buffers first, so that a bad entry changes nothing
     for (int n = n_hi; n >= n_lo; --n) {
         const int i = n - n_lo;   // mus[i] = mu^n, mus[i+1] = mu^{n+1}, mus[i+2] = mu^{n+2}
         const float *m2 = mus[i + 2], *m1 = mus[i + 1];
         float *m0 = mus[i];
         if (!m2 || !m0 || (n >= 1 && !m1)) return MMS_EINVAL;
-        const float *un = (grad && n >= 1) ? us[i] : nullptr;
-        if (grad && n >= 1 && !un) return MMS_EINVAL;
         if (m1 && n >= 1 && overlap(m1, bytes, m0, bytes)) return MMS_EINVAL;
         if (m2 != m0 && overlap(m2, bytes, m0, bytes)) return MMS_EINVAL;
-        if (un && overlap(un, bytes, m0, bytes)) return MMS_EINVAL;
+        if (!grad) continue;
+        if (n >= 1 && !keeps(n)) {
+            const float *un = us ? us[i] : nullptr;
+            if (!un || overlap(un, bytes, m0, bytes)) return MMS_EINVAL;
+        }
+        // a step may read the kept values of the level above its own, its own and the one below
+        for (int k = n - 1; k <= n + 1 && k <= n_hi; ++k)
+            if (const float *s = k >= 1 ? keeps(k) : nullptr)
+                if (!aligned16(s) || overlap(s, bytes, m0, bytes)) return MMS_EINVAL;
     }
     if (grid_empty(&w->g)) return MMS_OK;
     hipStream_t s = (hipStream_t)stream;
+    // Step n holds mu^{n+2}, mu^{n+1} and mu^n in registers, so it can add the gradient terms
+    // mu^{k+1} S(u^k) of k = n+1, n and n-1 from kept values.  Terms are added in order, up to
+    // three at a time where they belong to one block: a term that the next one joins waits for
+    // the next step, where it is the first of three.  `next` is the first term not added.
+    int next = n_hi;
+    const int lowest = n_lo > 1 ? n_lo : 1;
+    const int K = w->acc_block;
     for (int n = n_hi; n >= n_lo; --n) {
         const int i = n - n_lo;
-        const float *un = (grad && n >= 1) ? us[i] : nullptr;
+        const float *un = (grad && n >= 1 && !keeps(n)) ? us[i] : nullptr;
+        const float *sv[3] = {nullptr, nullptr, nullptr};
+        int first = 0, last = 0;
+        // whether term k can be added in one go with the term before it
+        auto joins = [&](int k) {
+            return k >= lowest && keeps(k) &&
+                   (K <= 1 || (w->nt - 1 - k) / K == (w->nt - 1 - (k + 1)) / K);
+        };
+        if (grad && n >= 1 && keeps(next) && (next == n + 1 || (next == n && !joins(n - 1)))) {
+            first = last = next--;
+            sv[n + 1 - first] = keeps(first);
+            while (next >= n - 1 && joins(next)) {
+                last = next--;
+                sv[n + 1 - last] = keeps(last);
+            }
+        }
         int rc = wave_adjoint_mu_step(w, n, mus[i + 2], mus[i + 1], mus[i], resid, un,
-                                      n >= 1 ? grad : nullptr, s);
+                                      last ? sv : nullptr, first, last, n >= 1 ? grad : nullptr, s);
         if (rc) return rc;
+        if (un) next = n - 1;
     }
     return MMS_OK;
+}
+
+int mms_wave_adjoint_mu(const mms_wave *w, int n_hi, int n_lo, float *const *mus,
+                        const float *const *us, const float *resid, double *grad, void *stream) {
+    return mms_wave_adjoint_mu_keep(w, n_hi, n_lo, mus, us, nullptr, resid, grad, stream);
 }
 
 int mms_wave_scale_mu(const mms_wave *w, const float *in, float *out, int dir, void *stream) {

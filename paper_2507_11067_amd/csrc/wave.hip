@@ -26,7 +26,10 @@ namespace {
 // ADJMU: the adjoint step carried in mu = C2 G lam, which has the forward step's form
 //   mu^n = G (2 mu^{n+1} - G mu^{n+2} + C2 S(mu^{n+1})) + C2 G R^T r^n
 // (one stencil stream, where the lam form forms C2 G lam from two)
-enum { MODE_FWD = 0, MODE_ADJ = 1, MODE_ENERGY = 2, MODE_GRAD = 3, MODE_ADJMU = 4 };
+// FWDKEEP: the forward step, S(u^n) written too (no image).
+// ADJACC: the mu form with gradient terms mu^{k+1} S(u^k) of kept stencil values S(u^k)
+enum { MODE_FWD = 0, MODE_ADJ = 1, MODE_ENERGY = 2, MODE_GRAD = 3, MODE_ADJMU = 4, MODE_ADJACC = 5,
+       MODE_FWDKEEP = 6 };
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
@@ -55,6 +58,9 @@ struct WaveArgs {
     int sponge_w;
     float sponge_a;
     int faces;
+    float *sout;          // FWDKEEP: S(u^n) for a later gradient
+    const float *s[3];    // ADJACC: S(u^{n+1}), S(u^n), S(u^{n-1}) for the terms with p0 = mu^{n+2},
+                          // ctr = mu^{n+1} and the result mu^n; NULL where a term is not added here
     int mu_form;          // GRAD, first adjoint step: the adjoint variable is mu = C2 G lam
 };
 
@@ -64,6 +70,11 @@ __device__ __forceinline__ float add_square(float s, float v) {
 #pragma clang fp contract(off)
     const float t = v * v;
     return s + t;
+}
+
+__device__ __forceinline__ float mul_rn(float a, float b) {
+#pragma clang fp contract(off)
+    return a * b;
 }
 
 // The point-wise part of a pass at a lane's four cells (z, y, x0 ..): the update with the
@@ -85,14 +96,16 @@ __device__ __forceinline__ void finish_cells(const WaveArgs &a, int z, int y, in
     const float p1v[4] = {pw1.x, pw1.y, pw1.z, pw1.w};
     const float cv[4] = {ctr.x, ctr.y, ctr.z, ctr.w};
     float r[4] = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (MODE == MODE_FWD || MODE == MODE_ADJMU) {
+    constexpr bool ADJM = MODE == MODE_ADJMU || MODE == MODE_ADJACC;
+    constexpr bool FW = MODE == MODE_FWD || MODE == MODE_FWDKEEP;
+    if constexpr (FW || ADJM) {
         // FWD: p0 = u^{n-1}, p1 = C2, ctr = u^n; ADJMU: p0 = mu^{n+2}, ctr = mu^{n+1}
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const float G = gz * gown[e];
             r[e] = G * (2.0f * cv[e] - G * p0v[e] + a.c2s * p1v[e] * o[e]);
         }
-        if constexpr (MODE == MODE_FWD) {
+        if constexpr (FW) {
             if (srcv != 0.f && z == a.src_z && y == a.src_y && a.src_x >= x0 &&
                 a.src_x < x0 + 4) {
 #pragma unroll
@@ -142,13 +155,24 @@ __device__ __forceinline__ void finish_cells(const WaveArgs &a, int z, int y, in
             for (int e = 0; e < 4; ++e)
                 if (x0 + e < g.nx) po[e] = r[e];
         }
-        if (MODE == MODE_FWD && a.traces && z == 0) {
+        if (FW && a.traces && z == 0) {
             float *pt = a.traces + (int64_t)y * g.nx + x0;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (x0 + e < g.nx) pt[e] = cv[e];
         }
-        if (MODE == MODE_FWD || MODE == MODE_GRAD) if (a.acc64) {
+        if (MODE == MODE_FWDKEEP) {
+            float *ps = a.sout + (int64_t)z * sz + off;
+            if (x0 + 3 < g.nx) {
+                const f4v v = {o[0], o[1], o[2], o[3]};
+                __builtin_nontemporal_store(v, reinterpret_cast<f4v *>(ps));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (x0 + e < g.nx) ps[e] = o[e];
+            }
+        }
+        if (MODE == MODE_FWD || MODE == MODE_GRAD || MODE == MODE_ADJACC) if (a.acc64) {
             // the accumulated term of each cell: FWD (u^{n+1})^2 (and of up to two levels
             // before it, oldest first), GRAD G lam^{n+1} S(u^n) (p0 = lam^{n+1}, o = S u^n); in
             // FP32 for the block partial, in FP64 for a direct update (add64)
@@ -157,22 +181,55 @@ __device__ __forceinline__ void finish_cells(const WaveArgs &a, int z, int y, in
             for (int e = 0; e < 4; ++e)
                 t[e] = a.mu_form ? p0v[e] * o[e]      // mu^{n+1} S(u^n), / c2 below
                                  : a.c2s * gz * gown[e] * p0v[e] * o[e];
+            // ADJACC: up to three terms, the one of the highest level first
+            float ta[3][4];
+            if constexpr (MODE == MODE_ADJACC) {
+                const float *mv[3] = {p0v, cv, r};
+                const int64_t zoff = (int64_t)z * sz + off;
+                float4 sv[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    sv[i] = *reinterpret_cast<const float4 *>((a.s[i] ? a.s[i] : a.c2) + zoff);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const float si[4] = {sv[i].x, sv[i].y, sv[i].z, sv[i].w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ta[i][e] = mul_rn(mv[i][e], si[e]);
+                }
+            }
+            (void)ta;
             // mu form: c2 G lam^{n+1} S(u^n) = mu^{n+1} S(u^n) / c2, with c2 the field
             // (C2 = c2s c2); the division is done in FP64 where a sum reaches acc64,
             // so the c2 field is read (cell by cell) once per block of steps
-            const bool div_c2 = MODE == MODE_GRAD && a.mu_form;
+            const bool div_c2 = MODE == MODE_ADJACC || (MODE == MODE_GRAD && a.mu_form);
             const float *c2row = a.c2 + (int64_t)z * sz + off;
             auto fin = [&](int e, double v) -> double {
                 return div_c2 ? v / (double)c2row[e] : v;
             };
             auto add64 = [&](int e, double v) -> double {
                 if constexpr (MODE == MODE_GRAD) return v + fin(e, (double)t[e]);
+                if constexpr (MODE == MODE_ADJACC) {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        if (a.s[i]) v += fin(e, (double)ta[i][e]);
+                    return v;
+                }
                 if (a.lag == 2) v += (double)p0v[e] * (double)p0v[e];
                 if (a.lag >= 1) v += (double)cv[e] * (double)cv[e];
                 return v + (double)r[e] * (double)r[e];
             };
             auto add32 = [&](int e, float v) -> float {
                 if constexpr (MODE == MODE_GRAD) return a.part_first ? t[e] : v + t[e];
+                if constexpr (MODE == MODE_ADJACC) {
+                    bool have = !a.part_first;
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        if (a.s[i]) {
+                            v = have ? v + ta[i][e] : ta[i][e];
+                            have = true;
+                        }
+                    return v;
+                }
                 v = a.part_first ? 0.f : v;
                 if (a.lag == 2) v = add_square(v, p0v[e]);
                 if (a.lag >= 1) v = add_square(v, cv[e]);
@@ -384,7 +441,7 @@ __global__ void __launch_bounds__(WNT) wave_kernel(WaveArgs a) {
     __syncthreads();
 
     const float *c = a.c;
-    const float srcv = (MODE == MODE_FWD && a.src) ? *a.src : 0.f;
+    const float srcv = ((MODE == MODE_FWD || MODE == MODE_FWDKEEP) && a.src) ? *a.src : 0.f;
     double esum = 0.0, ebad = 0.0;
     for (int z = zb; z < ze;) {
 #pragma unroll
@@ -489,7 +546,7 @@ __global__ void __launch_bounds__(256) wave_direct_kernel(WaveArgs a, unsigned n
     const bool part = MODE == MODE_GRAD && a.part && !a.part_first && x0 + 3 < g.nx && (dense & 3) == 0;
     const float4 pw0 = ld(a.p0 + zoff);
     const float4 pw1 = MODE != MODE_GRAD ? ld(a.c2 + zoff) : ld(part ? a.part + dense : a.c2);
-    const float srcv = (MODE == MODE_FWD && a.src) ? *a.src : 0.f;
+    const float srcv = ((MODE == MODE_FWD || MODE == MODE_FWDKEEP) && a.src) ? *a.src : 0.f;
     const int W = a.sponge_w;
     const float sa = a.sponge_a;
     float gown[4];
@@ -607,7 +664,7 @@ WaveArgs base_args(const mms_wave *w) {
 template <int MODE>
 int launch_mode(WaveArgs &a, const mms_grid *gd, int r, hipStream_t s) {
     fill_sizes(a.g, gd);
-    if constexpr (MODE == MODE_FWD || MODE == MODE_ADJMU || MODE == MODE_GRAD) {
+    if constexpr (MODE != MODE_ADJ && MODE != MODE_ENERGY) {
         if ((int64_t)a.g.nx * a.g.ny * a.g.nz <= DIRECT_MAX) {
             const unsigned nxw = (unsigned)(a.g.nx + 3) / 4;
             const unsigned nwords = nxw * (unsigned)a.g.ny * (unsigned)a.g.nz;
@@ -657,8 +714,9 @@ int launch_mode(WaveArgs &a, const mms_grid *gd, int r, hipStream_t s) {
 
 // lag: terms of earlier levels that the step adds to the image with its own (0 to 2), or -1 to
 // leave the image to a later step of the same call
+// (sout: S(u^n) too, or NULL)
 int wave_step(const mms_wave *w, int n, const float *up, const float *uc, float *un, int lag,
-              hipStream_t s) {
+              float *sout, hipStream_t s) {
     WaveArgs a = base_args(w);
     const int64_t o = (int64_t)w->g.halo * (w->g.sz + w->g.sy + 1);
     a.f0 = uc + o;
@@ -667,6 +725,7 @@ int wave_step(const mms_wave *w, int n, const float *up, const float *uc, float 
     a.traces = w->traces ? w->traces + (int64_t)n * w->g.ny * w->g.nx : nullptr;
     a.acc64 = lag >= 0 ? w->image : nullptr;
     a.lag = lag;
+    a.sout = sout ? sout + o : nullptr;
     if (a.acc64 && w->acc_block > 1) {
         const int K = w->acc_block, ph = (n - 1) % K;
         a.part = w->acc_part;
@@ -677,6 +736,7 @@ int wave_step(const mms_wave *w, int n, const float *up, const float *uc, float 
     a.src_z = (int)w->src_z;
     a.src_y = (int)w->src_y;
     a.src_x = (int)w->src_x;
+    if (sout) return launch_mode<MODE_FWDKEEP>(a, &w->g, w->radius, s);
     return launch_mode<MODE_FWD>(a, &w->g, w->radius, s);
 }
 
@@ -714,8 +774,11 @@ int wave_adjoint_step(const mms_wave *w, int n, const float *l2, const float *l1
     return launch_mode<MODE_GRAD>(b, &w->g, w->radius, s);
 }
 
+// kept: S(u^{n+1}), S(u^n), S(u^{n-1}) of the gradient terms that this step adds from kept
+// stencil values (NULL where it does not; the terms run from first down to last), or NULL
 int wave_adjoint_mu_step(const mms_wave *w, int n, const float *m2, const float *m1, float *m0,
-                         const float *resid, const float *un, double *grad, hipStream_t s) {
+                         const float *resid, const float *un, const float *const *kept, int first,
+                         int last, double *grad, hipStream_t s) {
     WaveArgs a = base_args(w);
     const int64_t o = (int64_t)w->g.halo * (w->g.sz + w->g.sy + 1);
     a.p0 = m2 + o;
@@ -729,8 +792,21 @@ int wave_adjoint_mu_step(const mms_wave *w, int n, const float *m2, const float 
         return check_launch("adjoint_first_kernel");
     }
     a.f0 = m1 + o;
-    const int rc = launch_mode<MODE_ADJMU>(a, &w->g, w->radius, s);
-    if (rc || !grad) return rc;
+    int rc;
+    if (kept) {
+        a.acc64 = grad;
+        for (int i = 0; i < 3; ++i) a.s[i] = kept[i] ? kept[i] + o : nullptr;
+        if (w->acc_block > 1) {
+            const int K = w->acc_block;
+            a.part = w->acc_part;
+            a.part_first = (w->nt - 1 - first) % K == 0;
+            a.part_last = (w->nt - 1 - last) % K == K - 1 || last == 1;
+        }
+        rc = launch_mode<MODE_ADJACC>(a, &w->g, w->radius, s);
+    } else {
+        rc = launch_mode<MODE_ADJMU>(a, &w->g, w->radius, s);
+    }
+    if (rc || !grad || !un) return rc;
     // gradient terms mu^{n+1} S(u^n) / c2 (the division where a sum reaches grad)
     WaveArgs b = base_args(w);
     b.f0 = un + o;

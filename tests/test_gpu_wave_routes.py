@@ -98,3 +98,44 @@ def test_image_is_the_same_however_steps_are_called(dims, block):
     assert torch.isfinite(images[0]).all() and images[0].max() > 0
     for i in images[1:]:
         assert torch.equal(images[0], i)
+
+
+@pytest.mark.parametrize("block", [1, 2, 8])
+@pytest.mark.parametrize("dims", [(37, 22, 18), (327, 118, 97), (43, 301, 293)],
+                         ids=["direct", "marching", "flat"])
+def test_gradient_from_kept_stencil_values_is_the_same(dims, block):
+    """The gradient of 13 adjoint steps from forward levels, and from the stencil values S(u^n)
+    that the forward steps kept of all, of some and of one of them."""
+    import paper_2507_11067_amd as mms
+    grid, nt = mms.Grid(*dims), 14
+    c2, u0, u1, d = fields(grid, 4, 7)
+    w = mms.Wave(grid, c2, weights(4), nt, sponge_width=4, sponge_alpha=0.1, sponge_faces=63)
+    us = [u0, u1] + [grid.zeros(DEV) for _ in range(nt - 1)]
+    keep = [grid.zeros(DEV).fill_(float("nan")) for _ in range(nt - 1)]
+    plain = [u0, u1] + [grid.zeros(DEV) for _ in range(nt - 1)]
+    w.forward(1, nt, plain)
+    w.forward_keep(1, nt, us, keep)          # keep[n - 1] = S(u^n)
+    dense = (grid.nz, grid.ny, grid.nx)
+    part = torch.empty(dense, device=DEV)
+    resid = torch.ones((nt, grid.ny, grid.nx), device=DEV)
+
+    def run(kept):
+        w.set_accumulation(part, block)
+        mus = [d.clone(), grid.zeros(DEV)]
+        grad = torch.zeros(dense, dtype=torch.float64, device=DEV)
+        w.adjoint_mu_keep(nt - 1, 0, [mus[i % 2] for i in range(nt + 2)],
+                          [None if k is not None else u for k, u in zip(kept, us)], kept, resid, grad)
+        return [grid.interior(t) for t in mus] + [grad]
+
+    mus = [d.clone(), grid.zeros(DEV)]
+    ref = torch.zeros(dense, dtype=torch.float64, device=DEV)
+    w.set_accumulation(part, block)
+    w.adjoint_mu(nt - 1, 0, [mus[i % 2] for i in range(nt + 2)], us=us, resid=resid, grad=ref)
+    ref = [grid.interior(t) for t in mus] + [ref]
+    every = [None] + keep
+    for kept in (every, [k if i % 5 else None for i, k in enumerate(every)],
+                 [k if i == 6 else None for i, k in enumerate(every)], [None] * nt):
+        for a, b in zip(run(kept), ref):
+            assert torch.isfinite(b).all() and torch.equal(a, b)
+    for a, b in zip(us, plain):
+        assert torch.equal(a, b)
