@@ -139,3 +139,47 @@ def test_gradient_from_kept_stencil_values_is_the_same(dims, block):
             assert torch.isfinite(b).all() and torch.equal(a, b)
     for a, b in zip(us, plain):
         assert torch.equal(a, b)
+
+
+def passes_of_large_grids(grid, c2, a, b, u, r):
+    """One forward step without and with an image, with kept stencil values, and one adjoint step
+    with the gradient from kept values and from a forward level."""
+    import paper_2507_11067_amd as mms
+    dense = (grid.nz, grid.ny, grid.nx)
+    image, grad, grad2 = (torch.zeros(dense, dtype=torch.float64, device=DEV) for _ in range(3))
+    un, ui, uk, s, m0, m1 = (grid.zeros(DEV) for _ in range(6))
+    w = mms.Wave(grid, c2, weights(r), 8)
+    w.step(3, a, b, un)
+    w.forward_keep(3, 4, [a, b, uk], [s])
+    w.adjoint_mu_keep(5, 5, [m0, b, a], [None], [u], grad=grad)
+    w.adjoint_mu(5, 5, [m1, b, a], us=[u], grad=grad2)
+    w.set_image(image)
+    w.step(3, a, b, ui)
+    part = torch.ones(dense, device=DEV)
+    w.set_accumulation(part, 4)     # step 4 is the second of its block: the partial is read
+    grad3 = torch.zeros(dense, dtype=torch.float64, device=DEV)
+    w.adjoint_mu(3, 3, [m1, b, a], us=[u], grad=grad3)
+    torch.cuda.synchronize()
+    return [grid.interior(t) for t in (un, ui, uk, s, m0, m1)] + [image, grad, grad2, grad3, part]
+
+
+# a grid of at least 13 * 2^20 points and a part of it that an other kernel runs
+LARGE = {"direct": ((327, 230, 190), (61, 35, 29), (141, 150, 148)),
+         "marching": ((240, 241, 243), (239, 190, 183), (1, 20, 52)),
+         "flat": ((97, 384, 381), (61, 379, 300), (16, 2, 24))}
+
+
+@pytest.mark.parametrize("r", [1, 2, 3, 4])
+@pytest.mark.parametrize("kind", LARGE)
+def test_large_grids_agree_bitwise(kind, r):
+    import paper_2507_11067_amd as mms
+    dims, part, (x0, y0, z0) = LARGE[kind]
+    big, small = mms.Grid(*dims), mms.Grid(*part)
+    assert big.points >= 13 << 20 and small.points < 13 << 20
+    assert (small.points <= DIRECT_MAX) == (kind == "direct")
+    f = fields(big, 4, 30 + r)
+    res = (passes_of_large_grids(big, *f, r),
+           passes_of_large_grids(small, *(cut(t, big, small, z0, y0, x0) for t in f), r))
+    Z, Y, X = slice(z0, z0 + small.nz), slice(y0, y0 + small.ny), slice(x0, x0 + small.nx)
+    for k, (p, q) in enumerate(zip(*res)):
+        assert torch.isfinite(q).all() and torch.equal(p[Z, Y, X], q), k
