@@ -7,12 +7,16 @@
 // are the axis parts of the star.  Only H needs x and y neighbours and only V
 // needs z neighbours, so (following the paper's decomposition of complex kernels
 // into one-dimensional stencils on small blocks, Sec. IV-G):
-//  * H travels through a double-buffered LDS tile (x/y halo), requested one plane
-//    ahead straight from memory into LDS (no staging registers), together with the
-//    neighbouring tiles;
+//  * H travels through a double-buffered LDS tile (x/y halo);
 //  * V travels through a register queue of 2r+1 planes (z terms only);
-//  * the five point-wise operands (H^{n-1}, V^{n-1}, C2, a, b) are requested one
-//    plane ahead; both outputs are written with streaming stores.
+//  * both outputs are written with streaming stores.
+// The step is bound by the memory system (36 bytes a point; radius 2 takes as long as radius 4 at
+// 400^3), so its requests must not stop: each operand's registers are requested anew as soon as
+// the plane in hand has used them (point-wise operands and the H tile one plane ahead, V two),
+// after the stores, so that a wait counts younger requests only, and across the barrier.  Loads
+// straight into LDS cannot stay in flight there (the barrier waits for all of them): with them
+// the kernel took, us a step at radius 4, before / now: 160^3 31.5 / 28.7, 200^3 53.8 / 51.3,
+// 301 x 255 x 290 186 / 177, 400^3 509 / 499 (4.6 TB/s); radius 2, 240 x 250 x 230: 115 / 108.
 // Small grids take a direct kernel, narrow ones flat tiles (see DIRECT_MAX, FLAT_MAX_NX).  us a
 // step, radius 4, before / with them: 64^3 13.9 / 10.8 (the host's side of a call),
 // 128^3 19.6 / 17.2, 47 x 300 x 300 67.9 / 34.6, 100 x 300 x 300 87.1 / 70.3.
@@ -40,12 +44,6 @@ struct VtiArgs {
     float sponge_a;
     int faces;
 };
-
-// One 16-byte word per lane from memory straight into LDS: lane l's word lands at
-// dst + l (dst the same for the whole wave); completion is counted by vmcnt.
-__device__ __forceinline__ void load_lds16(const float *src, float4 *dst) {
-    __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
-}
 
 // Point-wise operands of four cells: H^{n-1}, V^{n-1}, C2, a, b
 struct Pw {
@@ -119,10 +117,7 @@ __global__ void __launch_bounds__(VNT) vti_kernel(VtiArgs a) {
     constexpr int NT = VNT;
     constexpr int NL = flat_tile_words(R, NT);   // words of the largest H tile, row-major
     constexpr int NLK = (NL + NT - 1) / NT;
-    // two arrays, each step's buffer fixed at compile time (phases in pairs), so that the
-    // compiler does not wait on the direct loads before the current plane's reads
-    __shared__ float4 tile0[NL];
-    __shared__ float4 tile1[NL];
+    __shared__ float4 tile[2][NL];
 
     const Geom &g = a.g;
     int b = mms_xcd_remap(blockIdx.x, gridDim.x);
@@ -152,14 +147,17 @@ __global__ void __launch_bounds__(VNT) vti_kernel(VtiArgs a) {
 
     const bool own_ok = lane_on && (x0 <= nx4) && (y < ylim);
     const int64_t own_off = (int64_t)y * sy + x0;
+    // lanes without cells in the array read the plane's first word (never used): an address
+    // select rather than a guard, so that no branch hides the number of requests in flight
+    const int64_t ld_off = own_ok ? own_off : 0;
     float gown[4];
     {
         const float gy = gaxis(y, g.ny, W, sa, a.faces & 4, a.faces & 8);
 #pragma unroll
         for (int e = 0; e < 4; ++e) gown[e] = gy * gaxis(x0 + e, g.nx, W, sa, a.faces & 1, a.faces & 2);
     }
-    auto ld = [&](const float *base, int z, int64_t off, bool ok) -> float4 {
-        return guarded_load(base + (int64_t)z * sz + off, ok, a.c2);
+    auto ld = [&](const float *base, int z) -> float4 {
+        return *reinterpret_cast<const float4 *>(base + (int64_t)z * sz + ld_off);
     };
     // H tile word i -> (row i / pitch, col i % pitch) from the tile origin (row yt - R, column
     // xt - 4); words outside this tile's lw columns or outside the array are read from the
@@ -172,87 +170,77 @@ __global__ void __launch_bounds__(VNT) vti_kernel(VtiArgs a) {
         const bool ok = (i < nw) && (col < lw) && (yt - R + row < ylim) && (xt - 4 + 4 * col <= nx4);
         d_off[k] = ok ? (uint32_t)row * (uint32_t)sy + 4u * (uint32_t)col : 0u;
     }
-    const int wave_base = __builtin_amdgcn_readfirstlane(tid & ~63);
-    auto load_tile = [&](int z, float4 *t) {
+    f4v st[NLK];
+    auto load_tile = [&](int z) {
         const float *p = a.hc + (int64_t)z * sz + (int64_t)(yt - R) * sy + (xt - 4);
 #pragma unroll
+        for (int k = 0; k < NLK; ++k) st[k] = *reinterpret_cast<const f4v *>(p + d_off[k]);
+    };
+    auto store_tile = [&](float4 *t) {
+#pragma unroll
         for (int k = 0; k < NLK; ++k)
-            if (tid + k * NT < nw) load_lds16(p + d_off[k], t + wave_base + k * NT);
+            if (tid + k * NT < nw) *reinterpret_cast<f4v *>(t + tid + k * NT) = st[k];
     };
 
     auto load_pw = [&](int z) {
         Pw p;
-        p.hp = ld(a.hp, z, own_off, own_ok);
-        p.vp = ld(a.vp, z, own_off, own_ok);
-        p.c2 = ld(a.c2, z, own_off, own_ok);
-        p.fa = ld(a.fa, z, own_off, own_ok);
-        p.fb = ld(a.fb, z, own_off, own_ok);
+        p.hp = ld(a.hp, z);
+        p.vp = ld(a.vp, z);
+        p.c2 = ld(a.c2, z);
+        p.fa = ld(a.fa, z);
+        p.fb = ld(a.fb, z);
         return p;
     };
 
-    float4 q[Q];          // V at planes z-R .. z+R
+    const int zl = ze - 1;
+    // V at planes z-R .. z+R, and z+R+1 (requested)
+    constexpr int QS = Q + 1;
+    float4 q[QS];
 #pragma unroll
-    for (int i = 0; i < Q; ++i) q[i] = ld(a.vc, zb - R + i, own_off, own_ok);
-    load_tile(zb, tile0);
+    for (int i = 0; i < Q; ++i) q[i] = ld(a.vc, zb - R + i);
+    load_tile(zb);
+    store_tile(tile[0]);
+    load_tile(min(zb + 1, zl));
     Pw pw = load_pw(zb);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    q[Q] = ld(a.vc, min(zb + 1, zl) + R);
     __syncthreads();
 
     const float *c = a.c;
     const float srcv = a.src ? *a.src : 0.f;
     const bool zlo = a.faces & 16, zhi = a.faces & 32;
-    // 2Q phases per round: the queue slot (ph mod Q) and the tile buffer (ph mod 2) are both
-    // compile-time indices
-    for (int z = zb; z < ze;) {
+    for (int z = zb;;) {
 #pragma unroll
-        for (int ph = 0; ph < 2 * Q; ++ph) {
-            if (z < ze) {
-                const bool more = z + 1 < ze;
-                float4 *cur = (ph & 1) ? tile1 : tile0;
-                float4 *nxt = (ph & 1) ? tile0 : tile1;
-                float4 nq = q[ph % Q];
-                Pw npw = pw;
-                if (more) {
-                    nq = ld(a.vc, z + R + 1, own_off, own_ok);
-                    load_tile(z + 1, nxt);
-                    npw = load_pw(z + 1);
-                }
-                const float4 *t = cur + own;
-                const float4 hc4 = t[0];
-                const float4 L = t[-1];
-                const float4 Rr = t[1];
-                const float w[12] = {L.x,   L.y,   L.z,   L.w,  hc4.x, hc4.y,
-                                     hc4.z, hc4.w, Rr.x, Rr.y, Rr.z,  Rr.w};
-                float sxy[4] = {0.f, 0.f, 0.f, 0.f}, szz[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int ph = 0; ph < QS; ++ph) {
+            const float4 *t = &tile[ph & 1][own];
+            const float4 hc4 = t[0];
+            const float4 L = t[-1];
+            const float4 Rr = t[1];
+            const float w[12] = {L.x,   L.y,   L.z,   L.w,  hc4.x, hc4.y,
+                                 hc4.z, hc4.w, Rr.x, Rr.y, Rr.z,  Rr.w};
+            float sxy[4] = {0.f, 0.f, 0.f, 0.f}, szz[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int k = -R; k <= R; ++k) {
-                    const float ck = c[R + k];
-                    const float4 vy = k == 0 ? hc4 : t[k * pitch];
-                    const float4 vz = q[(ph % Q + R + k + Q) % Q];
-                    const float yv[4] = {vy.x, vy.y, vy.z, vy.w};
-                    const float zv[4] = {vz.x, vz.y, vz.z, vz.w};
+            for (int k = -R; k <= R; ++k) {
+                const float ck = c[R + k];
+                const float4 vy = k == 0 ? hc4 : t[k * pitch];
+                const float4 vz = q[(ph + R + k) % QS];
+                const float yv[4] = {vy.x, vy.y, vy.z, vy.w};
+                const float zv[4] = {vz.x, vz.y, vz.z, vz.w};
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        sxy[e] = fmaf(ck, yv[e] + w[4 + e + k], sxy[e]);
-                        szz[e] = fmaf(ck, zv[e], szz[e]);
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    sxy[e] = fmaf(ck, yv[e] + w[4 + e + k], sxy[e]);
+                    szz[e] = fmaf(ck, zv[e], szz[e]);
                 }
-                const float gz = gaxis(z, g.nz, W, sa, zlo, zhi);
-                const float4 vc4 = q[(ph % Q + R) % Q];
-                float rh[4], rv[4];
-                update_cells(a, z, y, x0, gz, gown, hc4, vc4, sxy, szz, pw, srcv, rh, rv);
-                // the next H tile is in LDS once this lane's requests are done; the barrier
-                // publishes every lane's words and ends all reads of this plane; the output
-                // stores come after it, so that the wait does not cover them
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                __syncthreads();
-                if (lane_on && y < g.ny && x0 < g.nx) store_cells(a, z, y, x0, own_off, hc4, rh, rv);
-                if (more) {
-                    q[ph % Q] = nq;
-                    pw = npw;
-                }
-                ++z;
             }
+            const float gz = gaxis(z, g.nz, W, sa, zlo, zhi);
+            float rh[4], rv[4];
+            update_cells(a, z, y, x0, gz, gown, hc4, q[(ph + R) % QS], sxy, szz, pw, srcv, rh, rv);
+            store_tile(tile[(ph & 1) ^ 1]);
+            if (lane_on && y < g.ny && x0 < g.nx) store_cells(a, z, y, x0, own_off, hc4, rh, rv);
+            if (++z >= ze) return;
+            pw = load_pw(z);
+            load_tile(min(z + 1, zl));
+            q[ph] = ld(a.vc, min(z + 1, zl) + R);
+            __syncthreads();
         }
     }
 }
