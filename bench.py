@@ -540,7 +540,7 @@ def bench_tti(torch, mms, synth, dev, n=400, nt=300):
     bpp = 44.0      # fused minimum: p, q at n and n-1, C2, eps, delta, theta, phi; p, q out
     res = {"grid": [n, n, n], "steps": nt - 1, "ms_total": ms, "ms_per_step": ms / (nt - 1),
            "gpoints_s": gpts, "gbs": gpts * bpp, "hbm_frac": gpts * bpp / HBM_PEAK_GBS,
-           "algorithmic_bytes_per_point": bpp, "two_pass_bytes_per_point": 84.0,
+           "algorithmic_bytes_per_point": bpp,
            "sigma": TTI_SIGMA, "trace_max_abs": float(traces.abs().max().item()),
            "finite": bool(torch.isfinite(P[nt % 2]).all().item())}
     log(f"[bench] tti: {gpts:.1f} Gpoints/s ({ms:.0f} ms, {gpts * bpp:.0f} GB/s at 44 B/pt)")
@@ -893,22 +893,22 @@ COUNTED = {
     "box3": ("box_valu.hip", "box_valu_kernel<3", 8.0),
     "box4_bf16x3": ("box_mfma.hip", "box_mfma_kernel<4, 1,", 8.0),
     "box3_bf16x3": ("box_mfma.hip", "box_mfma_kernel<3, 1,", 8.0),
-    "wave": ("wave.hip", "wave_kernel<4, 0, 64", 16.0),   # 400^3 forward step, no image
+    "wave": ("wave.hip", "wave_pipe_kernel<4, 0", 16.0),     # 400^3 forward step, no image
     "vti": ("vti.hip", "vti_kernel<4", 36.0),                # 400^3 VTI step
-    "tti_dz": ("tti.hip", "tti_dz_kernel<4", 24.0),          # 400^3 TTI pass 1 (padded rows)
-    "tti": ("tti.hip", "tti_kernel<4", 60.0),                # 400^3 TTI pass 2
+    "tti": ("tti.hip", "tti_kernel<4", 44.0),                # 400^3 TTI step
     # 256^3 gradient workload: the mu-form adjoint pass (mu^{n+1}, mu^{n+2}, C2 read; mu^n
-    # written) and the gradient pass (u^n, mu^{n+1} read; FP32 block partial written at the
-    # first step of a block of 8, read and written in the next 6, read at the last, which
-    # reads and writes the FP64 sum: (12 + 6 * 16 + 28) / 8 = 17 B per point and launch)
-    "adjmu": ("wave.hip", "wave_kernel<4, 4, 64", 16.0),
-    "grad": ("wave.hip", "wave_kernel<4, 3, 64", 17.0),
+    # written), and the same pass where it adds the terms of three steps from their kept
+    # stencil values: a block of 8 steps takes three such launches, which read 8 kept fields and
+    # 2 FP32 block partials, write 2, and read and write the FP64 sum at the block's end:
+    # 16 + (32 + 8 + 8 + 16) / 3 = 37.3 B per point and launch
+    "adjmu": ("wave.hip", "wave_pipe_kernel<4, 4", 16.0),
+    "adjacc": ("wave.hip", "wave_pipe_kernel<4, 5", 37.3),
 }
-COUNTED_POINTS = {"wave": 400 ** 3, "vti": 400 ** 3, "tti_dz": 400 ** 3, "tti": 400 ** 3,
-                  "adjmu": 256 ** 3, "grad": 256 ** 3}
+COUNTED_POINTS = {"wave": 400 ** 3, "vti": 400 ** 3, "tti": 400 ** 3, "adjmu": 256 ** 3,
+                  "adjacc": 256 ** 3}
 # the --only command that launches each counted kernel, and its --steps / --warmup when the
 # defaults do not fit (one gradient run is 1000 forward and 1000 adjoint steps)
-COUNTED_ONLY = {"tti_dz": "tti", "adjmu": "gradient", "grad": "gradient"}
+COUNTED_ONLY = {"adjmu": "gradient", "adjacc": "gradient"}
 ONLY_STEPS = {"gradient": ("1", "0")}
 
 
@@ -1023,7 +1023,7 @@ def collect_counters(args):
     # 1b. kernel traces of the single-kernel commands (split MFMA boxes, wave, VTI)
     summary["trace_only"] = {}
     traced = {}
-    for name in ("box4_bf16x3", "box3_bf16x3", "wave", "vti", "tti_dz", "tti", "adjmu", "grad"):
+    for name in ("box4_bf16x3", "box3_bf16x3", "wave", "vti", "tti", "adjmu", "adjacc"):
         only = COUNTED_ONLY.get(name, name)
         if only not in traced:        # one run serves every kernel its command launches
             st, wu = ONLY_STEPS.get(only, ("200", "40"))

@@ -26,10 +26,11 @@ namespace {
 // ADJMU: the adjoint step carried in mu = C2 G lam, which has the forward step's form
 //   mu^n = G (2 mu^{n+1} - G mu^{n+2} + C2 S(mu^{n+1})) + C2 G R^T r^n
 // (one stencil stream, where the lam form forms C2 G lam from two)
-// FWDKEEP: the forward step without image, S(u^n) written too if sout is given.
+// FWD: the forward step without image, S(u^n) written too if sout is given; FWDIMG: with an image
+// (small grids take it for every step that keeps no S)
 // ADJACC: the mu form with gradient terms mu^{k+1} S(u^k) of kept stencil values S(u^k)
 enum { MODE_FWD = 0, MODE_ADJ = 1, MODE_ENERGY = 2, MODE_GRAD = 3, MODE_ADJMU = 4, MODE_ADJACC = 5,
-       MODE_FWDKEEP = 6 };
+       MODE_FWDIMG = 6 };
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
@@ -50,11 +51,11 @@ struct WaveArgs {
     float *out;           // u^{n+1} (FWD), lam^n (ADJ)
     float *traces;        // FWD: [ny][nx] plane of level n, or NULL
     const float *resid;   // ADJ: [ny][nx] plane of level n, or NULL
-    double *acc64;        // FWD: image, GRAD: grad (dense [nz][ny][nx]), or NULL
+    double *acc64;        // FWDIMG: image, GRAD: grad (dense [nz][ny][nx]), or NULL
     float *part;          // FP32 partial of the current block (image or grad), or NULL
     int part_first;       // with part: first step of a block (part = term)
     int part_last;        // with part: last step of a block (acc64 += part + term)
-    int lag;              // FWD: levels before u^{n+1} whose terms this step adds too (0, 1: u^n,
+    int lag;              // FWDIMG: levels before u^{n+1} whose terms this step adds too (0, 1: u^n,
                           // 2: u^{n-1} and u^n)
     double *partials;     // ENERGY: one (FP64 partial, non-finite count) pair per block
     const float *src;     // device pointer to dt^2 f^n, or NULL
@@ -62,7 +63,7 @@ struct WaveArgs {
     int sponge_w;
     float sponge_a;
     int faces;
-    float *sout;          // FWDKEEP: S(u^n) for a later gradient, or NULL
+    float *sout;          // FWD: S(u^n) for a later gradient, or NULL
     const float *s[3];    // ADJACC: S(u^{n+1}), S(u^n), S(u^{n-1}) for the terms with p0 = mu^{n+2},
                           // ctr = mu^{n+1} and the result mu^n; NULL where a term is not added here
     int mu_form;          // GRAD, first adjoint step: the adjoint variable is mu = C2 G lam
@@ -101,7 +102,7 @@ __device__ __forceinline__ void finish_cells(const WaveArgs &a, int z, int y, in
     const float cv[4] = {ctr.x, ctr.y, ctr.z, ctr.w};
     float r[4] = {0.f, 0.f, 0.f, 0.f};
     constexpr bool ADJM = MODE == MODE_ADJMU || MODE == MODE_ADJACC;
-    constexpr bool FW = MODE == MODE_FWD || MODE == MODE_FWDKEEP;
+    constexpr bool FW = MODE == MODE_FWD || MODE == MODE_FWDIMG;
     if constexpr (FW || ADJM) {
         // FWD: p0 = u^{n-1}, p1 = C2, ctr = u^n; ADJMU: p0 = mu^{n+2}, ctr = mu^{n+1}
 #pragma unroll
@@ -165,7 +166,7 @@ __device__ __forceinline__ void finish_cells(const WaveArgs &a, int z, int y, in
             for (int e = 0; e < 4; ++e)
                 if (x0 + e < g.nx) pt[e] = cv[e];
         }
-        if (MODE == MODE_FWDKEEP && a.sout) {
+        if (MODE == MODE_FWD && a.sout) {
             float *ps = a.sout + (int64_t)z * sz + off;
             if (x0 + 3 < g.nx) {
                 const f4v v = {o[0], o[1], o[2], o[3]};
@@ -176,8 +177,8 @@ __device__ __forceinline__ void finish_cells(const WaveArgs &a, int z, int y, in
                     if (x0 + e < g.nx) ps[e] = o[e];
             }
         }
-        if (MODE == MODE_FWD || MODE == MODE_GRAD || MODE == MODE_ADJACC) if (a.acc64) {
-            // the accumulated term of each cell: FWD (u^{n+1})^2 (and of up to two levels
+        if (MODE == MODE_FWDIMG || MODE == MODE_GRAD || MODE == MODE_ADJACC) if (a.acc64) {
+            // the accumulated term of each cell: FWDIMG (u^{n+1})^2 (and of up to two levels
             // before it, oldest first), GRAD G lam^{n+1} S(u^n) (p0 = lam^{n+1}, o = S u^n); in
             // FP32 for the block partial, in FP64 for a direct update (add64)
             float t[4];
@@ -445,7 +446,7 @@ __global__ void __launch_bounds__(WNT) wave_kernel(WaveArgs a) {
     __syncthreads();
 
     const float *c = a.c;
-    const float srcv = ((MODE == MODE_FWD || MODE == MODE_FWDKEEP) && a.src) ? *a.src : 0.f;
+    const float srcv = ((MODE == MODE_FWD || MODE == MODE_FWDIMG) && a.src) ? *a.src : 0.f;
     double esum = 0.0, ebad = 0.0;
     for (int z = zb; z < ze;) {
 #pragma unroll
@@ -548,7 +549,7 @@ __global__ void __launch_bounds__(WNT) wave_pipe_kernel(WaveArgs a) {
     constexpr int NHK = 1;      // halo words per lane (a tile has fewer than NT)
     // the field's requests go out ahead of the point-wise part, after it where the registers of
     // the FP64 accumulations leave no room (any spill costs more than this order gains)
-    constexpr bool EARLY = R < 4 || MODE == MODE_ADJMU || MODE == MODE_FWDKEEP;
+    constexpr bool EARLY = R < 4 || MODE == MODE_ADJMU || MODE == MODE_FWD;
     constexpr int NR = R + 2;   // LDS ring: planes z .. z+R+1
     __shared__ float4 ring[NR][TW];
 
@@ -669,7 +670,7 @@ __global__ void __launch_bounds__(WNT) wave_pipe_kernel(WaveArgs a) {
     __syncthreads();
 
     const float *c = a.c;
-    const float srcv = ((MODE == MODE_FWD || MODE == MODE_FWDKEEP) && a.src) ? *a.src : 0.f;
+    const float srcv = ((MODE == MODE_FWD || MODE == MODE_FWDIMG) && a.src) ? *a.src : 0.f;
     double esum = 0.0, ebad = 0.0;
     for (int z = zb; z < ze;) {
 #pragma unroll
@@ -749,7 +750,7 @@ __global__ void __launch_bounds__(256) wave_direct_kernel(WaveArgs a, unsigned n
     const bool part = MODE == MODE_GRAD && a.part && !a.part_first && x0 + 3 < g.nx && (dense & 3) == 0;
     const float4 pw0 = ld(a.p0 + zoff);
     const float4 pw1 = MODE != MODE_GRAD ? ld(a.c2 + zoff) : ld(part ? a.part + dense : a.c2);
-    const float srcv = ((MODE == MODE_FWD || MODE == MODE_FWDKEEP) && a.src) ? *a.src : 0.f;
+    const float srcv = ((MODE == MODE_FWD || MODE == MODE_FWDIMG) && a.src) ? *a.src : 0.f;
     const int W = a.sponge_w;
     const float sa = a.sponge_a;
     float gown[4];
@@ -957,8 +958,8 @@ int wave_step(const mms_wave *w, int n, const float *up, const float *uc, float 
     a.src_x = (int)w->src_x;
     // (without image, large grids take the instance that has no registers for one)
     if (sout || (!a.acc64 && w->g.nx * w->g.ny * w->g.nz >= PIPE_MIN))
-        return launch_mode<MODE_FWDKEEP>(a, &w->g, w->radius, s);
-    return launch_mode<MODE_FWD>(a, &w->g, w->radius, s);
+        return launch_mode<MODE_FWD>(a, &w->g, w->radius, s);
+    return launch_mode<MODE_FWDIMG>(a, &w->g, w->radius, s);
 }
 
 int wave_adjoint_step(const mms_wave *w, int n, const float *l2, const float *l1, float *l0,
