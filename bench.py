@@ -394,11 +394,13 @@ def bench_rtm(torch, mms, synth, dev, n=400, nt=2000):
         torch.cuda.synchronize()
         ms = a.elapsed_time(b)
         gpts = grid.points * (nt - 1) / (ms * 1e-3) / 1e9
-        # algorithmic bytes per point-step: u^n, u^{n-1}, C2 read, u^{n+1} written; the FP64
-        # image read and written (16 B), or per block of K steps: the FP32 partial written
-        # (4 B), updated K-2 times (8 B), then read once with one FP64 read-modify-write
-        # (20 B), i.e. 8 + 8/K B per step
-        bpp = 16.0 + ((16.0 if block == 1 else 8.0 + 8.0 / block) if with_image else 0.0)
+        # algorithmic bytes per point-step: u^n, u^{n-1}, C2 read, u^{n+1} written.  The
+        # image: a step adds the terms of up to three levels it holds, so the FP64 image is read
+        # and written (16 B) once per three steps, or per block of K steps, in m = ceil(K / 3)
+        # steps: the FP32 partial written (4 B), updated m - 2 times (8 B), then read with one
+        # FP64 read-modify-write (20 B), i.e. 8 + 8 m B per block
+        adds = -(-block // 3)
+        bpp = 16.0 + ((16.0 / 3 if block == 1 else 8.0 * (1 + adds) / block) if with_image else 0.0)
         res[key] = {"ms_total": ms, "ms_per_step": ms / (nt - 1), "gpoints_s": gpts,
                     "algorithmic_bytes_per_point": bpp, "gbs": gpts * bpp,
                     "hbm_frac": gpts * bpp / HBM_PEAK_GBS}
@@ -891,8 +893,8 @@ COUNTED = {
     "box2": ("box_valu.hip", "box_valu_kernel<2", 8.0),
     "box4": ("box_valu.hip", "box_valu_kernel<4", 8.0),
     "box3": ("box_valu.hip", "box_valu_kernel<3", 8.0),
-    "box4_bf16x3": ("box_mfma.hip", "box_mfma_kernel<4, 1,", 8.0),
-    "box3_bf16x3": ("box_mfma.hip", "box_mfma_kernel<3, 1,", 8.0),
+    "box4_bf16x3": ("box_mfma.hip", "box_mfma_kernel<4, 1>", 8.0),
+    "box3_bf16x3": ("box_mfma.hip", "box_mfma_kernel<3, 1>", 8.0),
     "wave": ("wave.hip", "wave_pipe_kernel<4, 0", 16.0),     # 400^3 forward step, no image
     "vti": ("vti.hip", "vti_kernel<4", 36.0),                # 400^3 VTI step
     "tti": ("tti.hip", "tti_kernel<4", 44.0),                # 400^3 TTI step
