@@ -66,7 +66,7 @@ struct MCfg {
 struct MfmaArgs {
     Geom g;
     float c[729];      // [dz][dy][dx]
-    float cscale;      // FP16 path: power-of-two scale of the weights
+    int cexp;          // FP16 path: the weights are scaled by 2^cexp
 };
 
 // FP32 -> BF16 with round to nearest even (one v_cvt_pk_bf16_f32 on gfx950).
@@ -173,7 +173,7 @@ __global__ void __launch_bounds__(64 * MCfg<R>::NW) box_mfma_kernel(MfmaArgs a) 
     }
     const int z_first = zb - R, z_last = ze + R;
 
-    const float cscale = (PREC == MMS_FP16X3S) ? a.cscale : 1.0f;
+    const float cscale = (PREC == MMS_FP16X3S) ? ldexpf(1.0f, a.cexp) : 1.0f;
 
     // Toeplitz fragments of every dz into LDS (A operand), from a copy of the weights that
     // borrows the plane buffer
@@ -234,10 +234,13 @@ __global__ void __launch_bounds__(64 * MCfg<R>::NW) box_mfma_kernel(MfmaArgs a) 
     };
     // FP16 path: one power-of-two scale per block and step, from the largest finite |x| that
     // the block has staged so far.  It only changes when a step brings a larger value: the
-    // accumulators, which hold sums in units of dscale * cscale, are then rescaled (exactly).
+    // accumulators, which hold sums in units of 2^-(dexp + cexp), are then rescaled (exactly).
     // A scan of the block's whole window before the first product would cost a second read
     // of the grid (0.15 of 0.9 ms at 512^3, radius 4).
-    float dscale = 1.0f, dnext = 1.0f, dmax = 0.f;
+    // The scales are held as exponents: an output leaves by one exact multiplication with
+    // 2^-(data + weights), where the product of two factors could overflow or underflow on the way.
+    int dexp = 0, dnext = 0;
+    float dmax = 0.f;
     auto scale_step = [&]() {
         float m = 0.f;
 #pragma unroll
@@ -260,22 +263,23 @@ __global__ void __launch_bounds__(64 * MCfg<R>::NW) box_mfma_kernel(MfmaArgs a) 
             dmax = m;
             int e;
             frexpf(m, &e);  // m = f 2^e, 0.5 <= f < 1
-            dnext = ldexpf(1.0f, min(14 - e, 100));
+            dnext = min(14 - e, 127);
         }
     };
     // the split runs while the previous step's MFMAs execute; only the LDS writes wait
     // for the barrier that frees the plane buffer
     auto split_plane = [&]() {
+        const float sc = PREC == MMS_FP16X3S ? ldexpf(1.0f, dnext) : 1.0f;
 #pragma unroll
         for (int k = 0; k < NSK; ++k) {
             uint32_t h[4], l[4];
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 uint16_t h0, l0, h1, l1, h2, l2, h3, l3;
-                split<PREC>(stage[k][j].x, dnext, h0, l0);
-                split<PREC>(stage[k][j].y, dnext, h1, l1);
-                split<PREC>(stage[k][j].z, dnext, h2, l2);
-                split<PREC>(stage[k][j].w, dnext, h3, l3);
+                split<PREC>(stage[k][j].x, sc, h0, l0);
+                split<PREC>(stage[k][j].y, sc, h1, l1);
+                split<PREC>(stage[k][j].z, sc, h2, l2);
+                split<PREC>(stage[k][j].w, sc, h3, l3);
                 h[2 * j] = h0 | (uint32_t)h1 << 16;
                 h[2 * j + 1] = h2 | (uint32_t)h3 << 16;
                 l[2 * j] = l0 | (uint32_t)l1 << 16;
@@ -324,7 +328,7 @@ __global__ void __launch_bounds__(64 * MCfg<R>::NW) box_mfma_kernel(MfmaArgs a) 
     load_plane(z_first);
     if constexpr (PREC == MMS_FP16X3S) scale_step();
     split_plane();
-    dscale = dnext;
+    dexp = dnext;
     __syncthreads();   // the weights' copy is read
     write_plane();
     if (z_first + PZ < z_last) load_plane(z_first + PZ);
@@ -400,7 +404,7 @@ __global__ void __launch_bounds__(64 * MCfg<R>::NW) box_mfma_kernel(MfmaArgs a) 
 #pragma unroll
         for (int u = NU / 2; u < NU; ++u) unit(u);
         // output planes zi - R .. zi - R + PZ - 1 are complete (those outside [zb, ze) are dropped)
-        const float od = 1.0f / dscale, oc = 1.0f / cscale;
+        const int oexp = -(dexp + a.cexp);
 #pragma unroll
         for (int j = 0; j < PZ; ++j) {
             const int zo = zi - R + j;
@@ -413,7 +417,8 @@ __global__ void __launch_bounds__(64 * MCfg<R>::NW) box_mfma_kernel(MfmaArgs a) 
                     float *po = g.out0 + (int64_t)zo * sz + (int64_t)y * sy + x;
                     const floatx4 s = acc[j][t];
                     const float4 o = PREC == MMS_FP16X3S
-                        ? make_float4(s[0] * od * oc, s[1] * od * oc, s[2] * od * oc, s[3] * od * oc)
+                        ? make_float4(ldexpf(s[0], oexp), ldexpf(s[1], oexp), ldexpf(s[2], oexp),
+                                      ldexpf(s[3], oexp))
                         : make_float4(s[0], s[1], s[2], s[3]);
                     if (x + 3 < g.nx) {
                         *reinterpret_cast<float4 *>(po) = o;
@@ -430,13 +435,14 @@ __global__ void __launch_bounds__(64 * MCfg<R>::NW) box_mfma_kernel(MfmaArgs a) 
 #pragma unroll
             for (int t = 0; t < NT; ++t)
                 acc[s][t] = s + PZ < NQ ? acc[s + PZ][t] : floatx4{0.f, 0.f, 0.f, 0.f};
-        if (PREC == MMS_FP16X3S && dnext != dscale) {
-            const float f = dnext / dscale;   // a power of two
+        if (PREC == MMS_FP16X3S && dnext != dexp) {
 #pragma unroll
             for (int s = 0; s < NQ; ++s)
 #pragma unroll
-                for (int t = 0; t < NT; ++t) acc[s][t] *= f;
-            dscale = dnext;
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[s][t][e] = ldexpf(acc[s][t][e], dnext - dexp);
+            dexp = dnext;
         }
         __syncthreads();   // every wave is done with plane zi
         if (zi + PZ < z_last) {
@@ -491,11 +497,11 @@ int launch_rp(const float *in, float *out, const mms_grid *gd, const float *coef
         const float v = coeffs[i] < 0 ? -coeffs[i] : coeffs[i];
         cmax = v > cmax ? v : cmax;
     }
-    a.cscale = 1.0f;
+    a.cexp = 0;
     if (PREC == MMS_FP16X3S && cmax > 0.f && cmax < 3.0e38f) {
         int e;
         frexpf(cmax, &e);
-        a.cscale = ldexpf(1.0f, 14 - e);
+        a.cexp = 14 - e < 127 ? 14 - e : 127;
     }
     const int64_t nblk = (int64_t)g.ntx * g.nty * g.nzc;
     if (nblk > 0x7fffffff) return MMS_EINVAL;
