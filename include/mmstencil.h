@@ -64,9 +64,10 @@ extern "C" {
 #define MMS_FP32 0     /* FP32 FMA on the vector ALUs                                 */
 #define MMS_BF16X3 1   /* MFMA, BF16 hi+lo split of data and weights, 3 products,   */
                        /* FP32 accumulation                                          */
-#define MMS_FP16X3S 2  /* MFMA, FP16 hi+lo split with a power-of-two scale per      */
-                       /* thread block and step of planes (data) and per call       */
-                       /* (weights), 3 products                                      */
+#define MMS_FP16X3S 2  /* MFMA, FP16 hi+lo split with a power-of-two scale (data:   */
+                       /* from the largest finite value of the planes that a thread */
+                       /* block has in hand, up to 12 of them, in its 64 x 32 or     */
+                       /* 64 x 64 tile with halo; weights: per call), 3 products     */
 #define MMS_BF16X1 3   /* MFMA, BF16 hi*hi only: reduced-accuracy reference variant  */
 
 typedef struct mms_grid {

@@ -232,15 +232,21 @@ __global__ void __launch_bounds__(64 * MCfg<R>::NW) box_mfma_kernel(MfmaArgs a) 
                 stage[k][j] = guarded_load(p + j * sy, s_ok[k][j], g.in0);
         }
     };
-    // FP16 path: one power-of-two scale per block and step, from the largest finite |x| that
-    // the block has staged so far.  It only changes when a step brings a larger value: the
-    // accumulators, which hold sums in units of 2^-(dexp + cexp), are then rescaled (exactly).
-    // A scan of the block's whole window before the first product would cost a second read
-    // of the grid (0.15 of 0.9 ms at 512^3, radius 4).
+    // FP16 path: one power-of-two scale per block and step, from the largest finite |x| of the
+    // step's planes and of the earlier ones that still feed a sum (the last 2r), so that it falls
+    // with the amplitudes as well as it rises.  Where it changes, the accumulators, which hold
+    // sums in units of 2^-(dexp + cexp), are rescaled: exactly, and without overflow, since all
+    // their terms lie within the window.  (A scale that only rises keeps few bits, or none, of
+    // quiet planes after a loud one: amplitudes that fall by 0.66 a plane over a chunk of 64 had
+    // errors of 0.3 of their own plane.)  A scan of the block's whole window before the first
+    // product would cost a second read of the grid (0.15 of 0.9 ms at 512^3, radius 4).
     // The scales are held as exponents: an output leaves by one exact multiplication with
     // 2^-(data + weights), where the product of two factors could overflow or underflow on the way.
+    constexpr int NPREV = (2 * R + PZ - 1) / PZ;   // earlier steps in the window
     int dexp = 0, dnext = 0;
-    float dmax = 0.f;
+    float mprev[NPREV];   // their maxima, the latest first
+#pragma unroll
+    for (int i = 0; i < NPREV; ++i) mprev[i] = 0.f;
     auto scale_step = [&]() {
         float m = 0.f;
 #pragma unroll
@@ -259,10 +265,15 @@ __global__ void __launch_bounds__(64 * MCfg<R>::NW) box_mfma_kernel(MfmaArgs a) 
         m = sm.smax[0];
 #pragma unroll
         for (int w = 1; w < NW; ++w) m = fmaxf(m, sm.smax[w]);
-        if (m > dmax) {
-            dmax = m;
+        float wmax = m;
+#pragma unroll
+        for (int i = NPREV - 1; i >= 0; --i) {
+            wmax = fmaxf(wmax, mprev[i]);
+            mprev[i] = i > 0 ? mprev[i - 1] : m;
+        }
+        if (wmax > 0.f) {   // (zeros fit any scale)
             int e;
-            frexpf(m, &e);  // m = f 2^e, 0.5 <= f < 1
+            frexpf(wmax, &e);  // wmax = f 2^e, 0.5 <= f < 1
             dnext = min(14 - e, 127);
         }
     };

@@ -1,7 +1,10 @@
-"""GPU parity of the split-precision box over the range of its values, against the FP64 oracle.
+"""GPU parity of the split-precision box over the range of its values: large and small operands,
+and amplitudes that change along z, against the FP64 oracle.
 
 Tolerance: the FP16 split keeps 22 bits of both operands, so a product is off by less than 2^-21
-of itself; 1e-5 of the largest output is the bound that every sweep of this library is held to.
+of itself; operands far below the largest one of their neighbourhood keep fewer, with an absolute
+error of 2^-38 of it.  The neighbourhoods below span less than 2^8, which leaves 2^-30: 1e-5 of
+the largest output is the bound that every sweep of this library is held to.
 """
 import numpy as np
 import pytest
@@ -38,3 +41,20 @@ def test_fp16_operands_of_any_magnitude(r, xs, cs):
     got = sweep(x, grid, r, c, "fp16x3s")
     assert np.isfinite(got).all()
     assert rel_errors(got, ref)[0] <= 1e-5
+
+
+@pytest.mark.parametrize("falling", [True, False], ids=["falling", "rising"])
+@pytest.mark.parametrize("r", [1, 2, 3, 4])
+def test_fp16_scale_follows_the_planes(r, falling):
+    """Amplitudes that change by a factor of 0.66 a plane, on a grid of 256 tiles, whose blocks
+    walk all 64 planes: every output plane is as accurate as its own neighbourhood allows."""
+    import paper_2507_11067_amd as mms
+    nx, ny, nz = 1024, 512 if r >= 3 else 1024, 64
+    grid = mms.Grid(nx, ny, nz)
+    x = synth.uniform_grid(410, nx, ny, nz, sy=grid.sy)
+    z = np.arange(nz + 8) - 4
+    x *= (0.66 ** (z if falling else nz - 1 - z)).astype(np.float32)[:, None, None]
+    c = synth.box_coeffs(411, r)
+    got, ref = sweep(x, grid, r, c, "fp16x3s"), interior(oracle.box(x, nx, ny, nz, r, c), grid)
+    errors = [rel_errors(got[k], ref[k])[0] for k in range(nz)]
+    assert max(errors) <= 1e-5, errors
