@@ -93,7 +93,8 @@ typedef struct mms_grid {
  * shapes; any of the four for the box.  The box MFMA variants recast each dz of the sweep as a
  * banded Toeplitz product over (y, x), the matrix-unit mapping of Sec. IV-A with the
  * one-dimensional stencils of the box decomposition of Sec. IV-C taken 4 x 4 outputs at a time.
- * There a NaN or Inf input cell makes NaN of outputs up to r + 3 cells away in y and 7 in x.
+ * A NaN or Inf input cell (BF16: also one that rounds to Inf) reaches the outputs whose box holds
+ * it and no others: they become NaN, in BF16X1 what its products with the weights make of them.
  * An FP32 box of radius 2-4 addresses a tile of (32 + 2r + 1) rows with 32-bit
  * offsets: a pitch sy with (33 + 2r) * sy >= 2^32 gives MMS_EUNSUPPORTED.
  */

@@ -33,6 +33,12 @@
 // whole step ahead and split halfway through it.  (step, dz) units that feed no output of
 // the chunk are skipped, which matters where chunks are short.
 //
+// Cells that are not finite.  A block's window holds cells that an output's box does not, with
+// zero weights, and 0 * NaN or 0 * Inf spoils that output.  So an output that is not finite is
+// formed again from the cells of its box alone, in FP32: the check is one FMA an output (512^3:
+// 0 to 1 %), and only what such a cell spoilt pays more.  (A bit map of such cells in LDS, with
+// zeros in their place in the products, cost 3 % of every sweep and 10 % of short ones.)
+//
 // The kernel is bound by the matrix cores: at 512^3, radius 4, it issues 1.46 PFLOP/s of
 // MFMA work (a large BF16 matrix product reaches 1.2 PFLOP/s on the same card).
 #include <hip/hip_runtime.h>
@@ -311,6 +317,40 @@ __global__ void __launch_bounds__(64 * MCfg<R>::NW) box_mfma_kernel(MfmaArgs a) 
         }
     };
 
+    // The four outputs from (x, y, zo) on from their boxes alone.  A cell or weight whose hi part
+    // is NaN or Inf makes an output NaN in the split forms (Inf - Inf in the lo part).
+    auto box_sums = [&](int x, int y, int zo, float *s) {
+        auto factor = [](float v) -> float {   // what a product of the variant takes v for
+            const float h = PREC == MMS_FP16X3S ? v : bf16_f(bf16_rn(v));
+            return !SPLIT3 ? h : fabsf(h) <= 3.402823466e38f ? v : __builtin_nanf("");
+        };
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] = 0.f;
+#pragma unroll 1
+        for (int dz = 0; dz < Q; ++dz) {
+            if (s[0] != s[0] && s[1] != s[1] && s[2] != s[2] && s[3] != s[3]) break;
+            const float *p = g.in0 + (int64_t)(zo + dz - R) * sz + (int64_t)(y - R) * sy + x;
+#pragma unroll 3
+            for (int dy = 0; dy < Q; ++dy, p += sy) {
+                float w[12];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const float4 v = *reinterpret_cast<const float4 *>(p - 4 + 4 * i);
+                    w[4 * i] = factor(v.x);
+                    w[4 * i + 1] = factor(v.y);
+                    w[4 * i + 2] = factor(v.z);
+                    w[4 * i + 3] = factor(v.w);
+                }
+#pragma unroll
+                for (int dx = -R; dx <= R; ++dx) {
+                    const float f = factor(a.c[(dz * Q + dy) * Q + dx + R]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s[e] = fmaf(f, w[4 + e + dx], s[e]);
+                }
+            }
+        }
+    };
+
     // acc[k][t] holds the partial sum of output plane zi - R + k
     constexpr int NQ = Q + PZ - 1;
     floatx4 acc[NQ][NT];
@@ -416,17 +456,20 @@ __global__ void __launch_bounds__(64 * MCfg<R>::NW) box_mfma_kernel(MfmaArgs a) 
         for (int u = NU / 2; u < NU; ++u) unit(u);
         // output planes zi - R .. zi - R + PZ - 1 are complete (those outside [zb, ze) are dropped)
         const int oexp = -(dexp + a.cexp);
+        const int x = xt + 4 * n;
+        float spoilt = 0.f;   // NaN if one of the lane's sums is not finite
 #pragma unroll
         for (int j = 0; j < PZ; ++j) {
             const int zo = zi - R + j;
             if (zo < zb || zo >= ze) continue;
-            const int x = xt + 4 * n;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const int y = yt + wrow + 4 * t + grp;
                 if (y < g.ny && x < g.nx) {
                     float *po = g.out0 + (int64_t)zo * sz + (int64_t)y * sy + x;
                     const floatx4 s = acc[j][t];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) spoilt = fmaf(s[e], 0.f, spoilt);
                     const float4 o = PREC == MMS_FP16X3S
                         ? make_float4(ldexpf(s[0], oexp), ldexpf(s[1], oexp), ldexpf(s[2], oexp),
                                       ldexpf(s[3], oexp))
@@ -439,6 +482,24 @@ __global__ void __launch_bounds__(64 * MCfg<R>::NW) box_mfma_kernel(MfmaArgs a) 
                         if (x + 2 < g.nx) po[2] = o.z;
                     }
                 }
+            }
+        }
+        if (spoilt != 0.f) {
+#pragma unroll 1
+            for (int i = 0; i < PZ * NT; ++i) {
+                const int zo = zi - R + i / NT, y = yt + wrow + 4 * (i % NT) + grp;
+                if (zo < zb || zo >= ze || y >= g.ny || x >= g.nx) continue;
+                float *po = g.out0 + (int64_t)zo * sz + (int64_t)y * sy + x;
+                bool on[4];   // the outputs to form again
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    on[e] = x + e < g.nx && !(fabsf(po[x + e < g.nx ? e : 0]) <= 3.402823466e38f);
+                if (!(on[0] || on[1] || on[2] || on[3])) continue;
+                float s[4];
+                box_sums(x, y, zo, s);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (on[e]) po[e] = s[e];
             }
         }
 #pragma unroll
