@@ -51,6 +51,8 @@ struct Pw {
 };
 
 // New values of both fields at the cells (z, y, x0 ..) from S_xy H, S_zz V and the operands.
+// The fused operations are spelt out: which product of a sum the compiler fuses, and so the
+// last bit, would otherwise differ from kernel to kernel.
 __device__ __forceinline__ void update_cells(const VtiArgs &a, int z, int y, int x0, float gz,
                                              const float *gown, const float4 &hc4,
                                              const float4 &vc4, const float *sxy, const float *szz,
@@ -66,8 +68,9 @@ __device__ __forceinline__ void update_cells(const VtiArgs &a, int z, int y, int
     for (int e = 0; e < 4; ++e) {
         const float G = gz * gown[e];
         const float C2 = a.c2s * c2v[e];
-        rh[e] = G * (2.0f * hcv[e] - G * hpv[e] + C2 * (fav[e] * sxy[e] + fbv[e] * szz[e]));
-        rv[e] = G * (2.0f * vcv[e] - G * vpv[e] + C2 * (fbv[e] * sxy[e] + szz[e]));
+        rh[e] = G * fmaf(C2, fmaf(fav[e], sxy[e], fbv[e] * szz[e]),
+                         fmaf(2.0f, hcv[e], -(G * hpv[e])));
+        rv[e] = G * fmaf(C2, fmaf(fbv[e], sxy[e], szz[e]), fmaf(2.0f, vcv[e], -(G * vpv[e])));
     }
     if (srcv != 0.f && z == a.src_z && y == a.src_y && a.src_x >= x0 &&
         a.src_x < x0 + 4) {
