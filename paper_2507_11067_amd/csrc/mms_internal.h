@@ -130,6 +130,22 @@ inline void flat_tile(Geom &g, int r, int nt, int64_t slots, int zmin) {
     g.nzc = (g.nz + g.zchunk - 1) / g.zchunk;
 }
 
+// Whether 32-bit element offsets from a tile's origin reach all of its rows and r more on each side.
+inline bool tile_offsets_fit(int rows, int r, int64_t sy) {
+    return (int64_t)(rows + 2 * r + 1) * sy < (int64_t)1 << 32;
+}
+
+// flat_tile for a kernel that addresses a tile's words with 32-bit offsets: a flat tile has up to
+// 128 rows, a wide one nt / 64, so a pitch may suit the one and not the other.  g is left as it
+// is, and the answer is false, where the flat tile does not fit.
+inline bool flat_tile32(Geom &g, int r, int nt, int64_t slots, int zmin) {
+    Geom f = g;
+    flat_tile(f, r, nt, slots, zmin);
+    if (!tile_offsets_fit(f.rows, r, g.sy)) return false;
+    g = f;
+    return true;
+}
+
 // Blocks of `kernel` (launched with `threads` threads, no dynamic LDS) that the
 // current device holds at once: CUs times resident blocks per CU.
 inline int64_t launch_slots(const void *kernel, int threads) {

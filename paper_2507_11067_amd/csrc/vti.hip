@@ -315,18 +315,17 @@ int vti_step(const mms_wave *w, int n, const float *fa, const float *fb, const f
     g.sy = gd->sy;
     g.sz = gd->sz;
     // the H tile is addressed with 32-bit offsets from its origin
-    if ((int64_t)(8 + 2 * w->radius + 1) * g.sy >= ((int64_t)1 << 32)) {
+    if (!tile_offsets_fit(VNT / 64, w->radius, g.sy)) {
         set_last_error("VTI step: grid rows too long for 32-bit tile offsets");
         return MMS_EUNSUPPORTED;
     }
-    const bool flat = g.nx <= FLAT_MAX_NX;
     g.txa = balanced_tile_words(g.nx, 64, &g.ntx);
     g.nty = (g.ny + 7) / 8;
     // one 512-thread block per CU (VGPR-bound), 256 CUs; the V queue fill costs
     // about one plane of traffic
     g.zchunk = pick_zchunk_rounds(g.nz, (int64_t)g.ntx * g.nty, 256, 8, 128, 1);
     g.nzc = (g.nz + g.zchunk - 1) / g.zchunk;
-    if (flat) flat_tile(g, w->radius, VNT, 256, 8);
+    const bool flat = g.nx <= FLAT_MAX_NX && flat_tile32(g, w->radius, VNT, 256, 8);
     const int r = w->radius;
     for (int k = -r; k <= r; ++k) a.c[k + r] = w->lap[k < 0 ? -k : k];
     const int64_t o = (int64_t)gd->halo * (gd->sz + gd->sy + 1);
