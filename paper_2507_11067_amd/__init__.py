@@ -70,11 +70,18 @@ class Grid:
         return _lib.MmsGrid(self.nx, self.ny, self.nz, self.halo, 0, self.sy, self.sz)
 
     def zeros(self, device="cuda", dtype=torch.float32) -> torch.Tensor:
+        return self._placed(torch.zeros, device, dtype)
+
+    def empty(self, device="cuda", dtype=torch.float32) -> torch.Tensor:
+        """zeros() without the fill."""
+        return self._placed(torch.empty, device, dtype)
+
+    def _placed(self, make, device, dtype) -> torch.Tensor:
         lead = self.lead if dtype == torch.float32 else 0
         if lead == 0:
-            return torch.zeros(self.shape, device=device, dtype=dtype)
+            return make(self.shape, device=device, dtype=dtype)
         n = self.shape[0] * self.shape[1] * self.shape[2]
-        return torch.zeros(lead + n, device=device, dtype=dtype)[lead:].view(self.shape)
+        return make(lead + n, device=device, dtype=dtype)[lead:].view(self.shape)
 
     def interior(self, t: torch.Tensor) -> torch.Tensor:
         H = self.halo

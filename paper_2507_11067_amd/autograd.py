@@ -129,7 +129,7 @@ class WavePropagate(torch.autograd.Function):
         inner = 0 if ctx.levels is not None else max(min(K, max(nt, 1)) - 2, 0)
         if mu_form:
             turn = [g.zeros(dev) for _ in range(min(inner, 2))]
-            keep = [torch.empty(g.shape, dtype=torch.float32, device=dev) for _ in range(inner)]
+            keep = [g.empty(dev) for _ in range(inner)]
         else:
             seg = [g.zeros(dev) for _ in range(inner)]
         grad = torch.zeros((g.nz, g.ny, g.nx), dtype=torch.float64, device=dev)
