@@ -88,10 +88,16 @@ class Grid:
         return t[H:H + self.nz, H:H + self.ny, H:H + self.nx]
 
 
+# The current stream's handle without the Stream object around it (2.7 us a call); a torch that
+# has no such function goes through the object.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> ctypes.c_void_p:
+    if stream is None and _raw_stream is not None:
+        return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
     if stream is None:
-        # the current stream's handle without the Stream object around it (2.7 us a call)
-        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        stream = torch.cuda.current_stream()
     return ctypes.c_void_p(stream.cuda_stream)
 
 
