@@ -16,7 +16,7 @@
 //
 // FP32 accuracy from 16-bit multipliers: every operand x is split as x = hi + lo
 // (BF16: hi = RN(x), lo = RN(x - hi); FP16: the same after scaling by a power of
-// two that keeps the block's largest |x| below 2^14), and each product is
+// two that keeps the largest |x| of the planes in hand below 2^14), and each product is
 // formed as hi*hi + hi*lo + lo*hi with FP32 accumulation (lo*lo is dropped, except
 // where a step has slots to spare).  The BF16X1 variant keeps hi*hi only.
 //

@@ -323,8 +323,10 @@ int launch_r(const float *in, float *out, const mms_grid *gd, const float *coeff
     // on, one of 1024 threads at radius 1.  A chunk's 2r halo planes feed about half their
     // outputs, so four planes stand for them and the block's start.  (With chunks of at least
     // 16 planes, 128 at radius 1, small grids left most CUs idle: 100^3 at radius 1 / 2 / 3 / 4
-    // took 163 / 53 / 143 / 253 us against 12 / 13 / 46 / 46; at 512^3 the chunk lengths, and
-    // the times, stay as they were.)
+    // took 163 / 53 / 143 / 253 us against 12 / 13 / 46 / 46.  At 512^3 the lengths stay as they
+    // were from radius 2 on.  Radius 1 is bound by HBM and reads two halo planes a chunk, but more
+    // blocks cover them: chunks of 128 planes / by rounds, us: 512^3 (43 planes) 233 / 227,
+    // 640 x 512 x 400 352 / 237, 300 x 301 x 290 211 / 72, 1024 x 1024 x 128 240 / 227.)
     const int zc = pick_zchunk_rounds(g.nz, cols, R == 1 ? 256 : 1024, 1, 128, 4);
     g.zchunk = zc;
     g.nzc = (g.nz + zc - 1) / zc;

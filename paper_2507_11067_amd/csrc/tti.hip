@@ -24,13 +24,16 @@
 //    phi; the update, with sponge, source and receivers, follows one step later, behind the
 //    barrier that ends the step (the only one);
 //  * the other operands are requested one plane ahead of their use; streaming stores.
-// LDS holds one block per CU (157 KB at radius 4), 8 waves, two per SIMD.  What bounds it:
-// the vector ALUs issue half of the time (about 590 instructions a plane and wave, 17 % of
-// them beside the other wave's), the rest are waits of waves in step; HBM is read almost
-// exactly once (2.4 GB against 2.3 at 400^3).  Measured at 400^3: 1160 -> 756 us a step
-// (radius 4), 1140 -> 724 (radius 2); 100^3 42 -> 24, 301 x 255 x 290 456 -> 287.  On the way:
-// one thread for both fields 1082 (registers), two halves 962, Dxy through the Dy ring and z
-// sums for Dzz 910, factored H1 848, one barrier a plane 796, angles a plane ahead 756.
+// LDS holds one block per CU (157 KB at radius 4), 8 waves, two per SIMD.  What bounds it is
+// latency: the vector ALUs issue half of the time (about 590 instructions a plane and wave at
+// radius 4, 17 % of them beside the other wave's), radius 2 takes nearly as long with half of
+// the FMAs, and HBM reads are near their least (2.49 GB against 2.30 at 400^3).  The rest are
+// waits of waves in step; several of the loop's loads, and a store, sit behind branches, so the
+// wait ahead of the LDS write covers every request in flight.
+// Measured at 400^3: 1160 -> 756 us a step (radius 4), 1140 -> 724 (radius 2); 100^3 42 -> 24,
+// 301 x 255 x 290 456 -> 287.  On the way: one thread for both fields 1082 (registers), two
+// halves 962, Dxy through the Dy ring and z sums for Dzz 910, factored H1 848, one barrier a
+// plane 796, angles a plane ahead 756.
 #include "mms_internal.h"
 
 namespace mms {
@@ -348,6 +351,7 @@ int launch_tti(const mms_wave *w, const mms_tti *t, int n, const float *pp, cons
                float *pn, const float *qp, const float *qc, float *qn, hipStream_t s) {
     const mms_grid *gd = &w->g;
     const int64_t o = (int64_t)gd->halo * (gd->sz + gd->sy + 1);
+    // (the pitch limit that the header states; this kernel's own offsets are 64-bit)
     if ((int64_t)(8 + 2 * R + 1) * gd->sy >= ((int64_t)1 << 32)) {
         set_last_error("TTI step: grid rows too long for 32-bit tile offsets");
         return MMS_EUNSUPPORTED;
