@@ -470,21 +470,22 @@ __global__ void __launch_bounds__(64 * MCfg<R>::NW) box_mfma_kernel(MfmaArgs a) 
                     const floatx4 s = acc[j][t];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) spoilt = fmaf(s[e], 0.f, spoilt);
-                    const float4 o = PREC == MMS_FP16X3S
-                        ? make_float4(ldexpf(s[0], oexp), ldexpf(s[1], oexp), ldexpf(s[2], oexp),
-                                      ldexpf(s[3], oexp))
-                        : make_float4(s[0], s[1], s[2], s[3]);
+                    floatx4 o = s;
+                    if constexpr (PREC == MMS_FP16X3S) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) o[e] = ldexpf(s[e], oexp);
+                    }
                     if (x + 3 < g.nx) {
-                        *reinterpret_cast<float4 *>(po) = o;
+                        *reinterpret_cast<floatx4 *>(po) = o;
                     } else {
-                        if (x + 0 < g.nx) po[0] = o.x;
-                        if (x + 1 < g.nx) po[1] = o.y;
-                        if (x + 2 < g.nx) po[2] = o.z;
+                        if (x + 0 < g.nx) po[0] = o[0];
+                        if (x + 1 < g.nx) po[1] = o[1];
+                        if (x + 2 < g.nx) po[2] = o[2];
                     }
                 }
             }
         }
-        if (spoilt != 0.f) {
+        if (__builtin_expect(spoilt != 0.f, 0)) {
 #pragma unroll 1
             for (int i = 0; i < PZ * NT; ++i) {
                 const int zo = zi - R + i / NT, y = yt + wrow + 4 * (i % NT) + grp;
