@@ -409,10 +409,11 @@ __global__ void __launch_bounds__(WNT) wave_kernel(WaveArgs a) {
         }
         return ld(a.f0, z, h_off[k], h_ok[k]);
     };
-    // tile of one plane (own cells + halo) into ring slot `slot`
+    // tile of one plane (own cells + halo) into ring slot `slot` (at `own`, which the reads have in
+    // a register: one more costs the lam-form adjoint of radius 4 a spill)
     auto ring_store = [&](int slot, const float4 &field, const float4 *halo) {
         float4 *t = &ring[slot][0];
-        if (lane_on) t[(R + ty) * pitch + tx + 1] = field;
+        if (lane_on) t[own] = field;
 #pragma unroll
         for (int k = 0; k < NHK; ++k)
             if (h_on[k]) t[h_lds[k]] = halo[k];
