@@ -88,7 +88,8 @@ __device__ __forceinline__ float mul_rn(float a, float b) {
 // sponge, source or receivers, its store, and the FP64 accumulations.  ctr and o: the stencil
 // field and S of it; pw0, pw1: the point-wise operands (see the modes in wave_kernel); off:
 // element offset of the cells within a plane; gown: the lane's sponge factors gy gx.
-template <int MODE>
+// ONE: the image takes the terms of this step alone (a.lag = 0).
+template <int MODE, bool ONE = false>
 __device__ __forceinline__ void finish_cells(const WaveArgs &a, int z, int y, int x0, int64_t off,
                                              bool live, float gz, const float *gown,
                                              const float4 &ctr, const float *o, const float4 &pw0,
@@ -221,8 +222,8 @@ __device__ __forceinline__ void finish_cells(const WaveArgs &a, int z, int y, in
                         if (a.s[i]) v += fin(e, (double)ta[i][e]);
                     return v;
                 }
-                if (a.lag == 2) v += (double)p0v[e] * (double)p0v[e];
-                if (a.lag >= 1) v += (double)cv[e] * (double)cv[e];
+                if (!ONE && a.lag == 2) v += (double)p0v[e] * (double)p0v[e];
+                if (!ONE && a.lag >= 1) v += (double)cv[e] * (double)cv[e];
                 return v + (double)r[e] * (double)r[e];
             };
             auto add32 = [&](int e, float v) -> float {
@@ -238,8 +239,8 @@ __device__ __forceinline__ void finish_cells(const WaveArgs &a, int z, int y, in
                     return v;
                 }
                 v = a.part_first ? 0.f : v;
-                if (a.lag == 2) v = add_square(v, p0v[e]);
-                if (a.lag >= 1) v = add_square(v, cv[e]);
+                if (!ONE && a.lag == 2) v = add_square(v, p0v[e]);
+                if (!ONE && a.lag >= 1) v = add_square(v, cv[e]);
                 return add_square(v, r[e]);
             };
             double *pa = a.acc64 + dense;
@@ -289,7 +290,11 @@ __device__ __forceinline__ void finish_cells(const WaveArgs &a, int z, int y, in
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         if (x0 + e < g.nx) {
-                            const float sum = add32(e, a.part_first ? 0.f : pp[e]);
+                            float sum;
+                            if constexpr (MODE == MODE_GRAD)
+                                sum = a.part_first ? t[e] : pp[e] + t[e];
+                            else
+                                sum = add32(e, a.part_first ? 0.f : pp[e]);
                             if (a.part_last)
                                 pa[e] += fin(e, (double)sum);
                             else
@@ -493,8 +498,15 @@ __global__ void __launch_bounds__(WNT) wave_kernel(WaveArgs a) {
                 }
                 const float gz = gaxis(z, g.nz, W, sa, zlo, zhi);
                 const bool live = lane_on && y < g.ny && x0 < g.nx;
-                finish_cells<MODE>(a, z, y, x0, own_off, live, gz, gown, ctr, o, pw0, pw1, srcv, esum,
-                                   ebad);
+                // (the image of a single step, without a choice at every cell: up to 2.5 % of the
+                // step; at radius 4 the second copy of the sums spills and loses 15 %)
+                constexpr bool SINGLE = MODE == MODE_FWDIMG && (R < 3 || (R == 3 && !FLAT));
+                if (SINGLE && a.lag == 0)
+                    finish_cells<MODE, SINGLE>(a, z, y, x0, own_off, live, gz, gown, ctr, o, pw0,
+                                               pw1, srcv, esum, ebad);
+                else
+                    finish_cells<MODE>(a, z, y, x0, own_off, live, gz, gown, ctr, o, pw0, pw1, srcv,
+                                       esum, ebad);
                 if (more) {
                     ring_store((z + R + 1) % NR, nq, hreg);
                     q[ph] = nq;
@@ -868,6 +880,23 @@ WaveArgs base_args(const mms_wave *w) {
     return a;
 }
 
+// Whether the kernel with requests across planes takes the pass.  From PIPE_MIN points on it does,
+// but for passes whose FP64 or FP32 sums would stop those requests: the sums are read when a cell
+// is finished, and a wait for them covers every request before them.  On rows that are not a
+// multiple of four cells they are four reads a lane, one after the other (us, pipe kernel / wave
+// kernel, 301 x 255 x 290: single step with FP64 image 179 / 166 at radius 2 or less and 195 / 171
+// at radius 4, lam-form gradient of radius 4 230 / 195; 8 steps at 301 x 255 x 250 with blocked
+// image, radius 4, 777 / 739); on other rows only a single step with FP64 sums loses (256^3, radius
+// 4, 104 / 100; with blocked sums 300 x 301 x 290 takes 131 / 142).
+template <int MODE>
+bool pipe_pays(const WaveArgs &a) {
+    if ((int64_t)a.g.nx * a.g.ny * a.g.nz < PIPE_MIN) return false;
+    constexpr bool sums = MODE == MODE_FWDIMG || MODE == MODE_GRAD || MODE == MODE_ADJACC;
+    if (!sums || !a.acc64) return true;
+    if (a.g.nx % 4) return false;
+    return MODE != MODE_FWDIMG || a.part || a.lag > 0;
+}
+
 template <int MODE>
 int launch_mode(WaveArgs &a, const mms_grid *gd, int r, hipStream_t s) {
     fill_sizes(a.g, gd);
@@ -896,7 +925,7 @@ int launch_mode(WaveArgs &a, const mms_grid *gd, int r, hipStream_t s) {
     if (nblk > 0x7fffffff) return MMS_EINVAL;
     const dim3 grid((unsigned)nblk), block(WNT);
     if constexpr (MODE != MODE_ADJ && MODE != MODE_ENERGY) {
-        if ((int64_t)a.g.nx * a.g.ny * a.g.nz >= PIPE_MIN) {
+        if (pipe_pays<MODE>(a)) {
             switch (2 * r + flat) {
                 case 2: hipLaunchKernelGGL((wave_pipe_kernel<1, MODE, false>), grid, block, 0, s, a); break;
                 case 3: hipLaunchKernelGGL((wave_pipe_kernel<1, MODE, true>), grid, block, 0, s, a); break;
